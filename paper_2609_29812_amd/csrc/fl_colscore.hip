@@ -4,9 +4,13 @@
 //     over the rows of a prefill), in two passes: the rows' log-normalisers, then the column sums;
 //   * the statistic that prunes a list for a smaller budget (Section 4.2): the mass the updated rows give
 //     each list entry, from their stored reference log-normalisers.
-// The dot products run on v_mfma_f64_16x16x4 (products of bf16 values are exact in fp64); every sum runs
-// in a fixed order (deterministic).
-#include "fl_common.h"
+// The dense statistic's dot products are integer products of byte digits (fl_digits.h), or v_mfma_f64_16x16x4
+// products (products of bf16 values are exact in fp64) where the digits do not hold the values; the list
+// statistic's are the latter.  Every sum runs in a fixed order (deterministic).
+#include "fl_attn_util.h"
+#include "fl_digits.h"
+
+#include <type_traits>
 
 namespace fl {
 
@@ -27,33 +31,34 @@ __device__ __forceinline__ void mfma_f64_layout(int l16, int kq, int (&row)[4], 
   }
 }
 
-// Dense column statistic in two passes, the fp64 dot products on v_mfma_f64_16x16x4 (products of bf16 values
-// are exact in fp64).  A wave owns 16 vectors of one side in registers (lane l holds dim 4s + l / 16 of vector
-// l % 16 for step s), a workgroup 64 of them; the other side is staged 32 vectors at a time in LDS as fp64.
+// Dense column statistic by v_mfma_f64_16x16x4 (products of bf16 values are exact in fp64), for the (batch,
+// head) pairs whose values the digits do not hold, in two passes.  A wave owns 16 vectors of one side in registers
+// (lane l holds dim 4s + l / 16 of vector l % 16 for step s), the workgroup 64 of them from vector wg_first on;
+// the other side is staged 32 vectors at a time in LDS as fp64.
 //   pass 1 (ROWS)  : the wave's 16 query rows against the staged K columns j <= i: per accumulator element
 //                    an online (max, sum) in fp64; the 16 partial pairs of a row are merged in column order;
 //   pass 2 (!ROWS) : the wave's 16 K columns against the staged query rows i >= j and their lse_i:
 //                    col_j = sum exp(l_ij - lse_i), the 16 partials of a column added in row order.
 // Every sum runs in a fixed order (deterministic).
+template <int D>
+struct CsWide {
+  double st[kCsRows * (D + 1)];           // padded stride: the 16 vectors of a read spread over banks
+  double lse[kCsRows];
+};
+struct CsMerge {
+  double v[4][16][16];
+};
+
 template <int D, bool ROWS>
-__global__ __launch_bounds__(256) void colscore_kernel(const uint16_t* __restrict__ q,
-                                                       const uint16_t* __restrict__ kc, int N, int H,
-                                                       double sigma, double* __restrict__ lse,
-                                                       float* __restrict__ col_key) {
-  constexpr int QS = D + 1;               // padded stride (doubles): the 16 vectors of a read spread over banks
+__device__ __forceinline__ void colscore_wide(const uint16_t* __restrict__ qbase, const uint16_t* __restrict__ kbase, int N, int H,
+                              double sigma, double* __restrict__ lse_bh, float* __restrict__ col_bh, int wg_first,
+                              CsWide<D>& wide, CsMerge& red_m, CsMerge& red_s) {
+  constexpr int QS = D + 1;
   constexpr int KSTEPS = D / 4;
-  __shared__ double st[kCsRows * QS];
-  __shared__ double st_lse[kCsRows];
-  __shared__ double red_m[4][16][17];
-  __shared__ double red_s[4][16][17];
-  const int h = blockIdx.y, b = blockIdx.z;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int l16 = lane & 15, kq = lane >> 4;
   const int64_t stride = (int64_t)H * D;
-  const uint16_t* qbase = q + (int64_t)b * N * stride + (int64_t)h * D;
-  const uint16_t* kbase = kc + (int64_t)b * N * stride + (int64_t)h * D;
-  double* lse_bh = lse + ((int64_t)b * H + h) * N;
-  const int v0 = blockIdx.x * 64 + wave * 16;          // first of the wave's own vectors
+  const int v0 = wg_first + wave * 16;                  // first of the wave's own vectors
   const bool wave_ok = v0 < N;
 
   double reg[KSTEPS];                                   // own vectors (query rows or key columns)
@@ -66,21 +71,21 @@ __global__ __launch_bounds__(256) void colscore_kernel(const uint16_t* __restric
   int el_r[4], el_c[4];                   // element t: staged vector el_r (A side), own vector el_c (B side)
   mfma_f64_layout(l16, kq, el_r, el_c);
   // staged range: pass 1 columns 0 .. last own row; pass 2 rows from the workgroup's first column on
-  const int wg_first = blockIdx.x * 64;
   const int s_begin = ROWS ? 0 : wg_first;
   const int s_end = ROWS ? min(N, wg_first + 64) : N;
   double m[4], acc[4];
 #pragma unroll
   for (int t = 0; t < 4; ++t) { m[t] = -INFINITY; acc[t] = 0.0; }
+  __syncthreads();
   for (int t0 = s_begin; t0 < s_end; t0 += kCsRows) {
     for (int x = threadIdx.x; x < kCsRows * D; x += 256) {
       const int r = x / D, dd = x % D;
       const int v = t0 + r;
-      st[r * QS + dd] = v < s_end ? (double)bf16_to_f32((ROWS ? kbase : qbase)[(int64_t)v * stride + dd]) : 0.0;
+      wide.st[r * QS + dd] = v < s_end ? (double)bf16_to_f32((ROWS ? kbase : qbase)[(int64_t)v * stride + dd]) : 0.0;
     }
     if (!ROWS && threadIdx.x < kCsRows) {
       const int v = t0 + (int)threadIdx.x;
-      st_lse[threadIdx.x] = v < s_end ? lse_bh[v] : 0.0;
+      wide.lse[threadIdx.x] = v < s_end ? lse_bh[v] : 0.0;
     }
     __syncthreads();
 #pragma unroll
@@ -90,7 +95,7 @@ __global__ __launch_bounds__(256) void colscore_kernel(const uint16_t* __restric
       const bool useful = wave_ok && sv0 < s_end && (ROWS ? sv0 <= v0 + 15 : sv0 + 15 >= v0);
       if (useful) {
         f64x4 d4 = {0.0, 0.0, 0.0, 0.0};
-        const double* sa = st + (16 * half + l16) * QS + kq;
+        const double* sa = wide.st + (16 * half + l16) * QS + kq;
 #pragma unroll
         for (int s = 0; s < KSTEPS; ++s) d4 = __builtin_amdgcn_mfma_f64_16x16x4f64(sa[4 * s], reg[s], d4, 0, 0, 0);
 #pragma unroll
@@ -108,7 +113,7 @@ __global__ __launch_bounds__(256) void colscore_kernel(const uint16_t* __restric
               }
             }
           } else {
-            if (sv < s_end && ov < N && sv >= ov) acc[t] += exp(l - st_lse[16 * half + el_r[t]]);   // row sv
+            if (sv < s_end && ov < N && sv >= ov) acc[t] += exp(l - wide.lse[16 * half + el_r[t]]);   // row sv
           }
         }
       }
@@ -118,8 +123,8 @@ __global__ __launch_bounds__(256) void colscore_kernel(const uint16_t* __restric
   // merge the 16 partials of each own vector in staged-slot order
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
-    red_m[wave][el_c[t]][el_r[t]] = m[t];
-    red_s[wave][el_c[t]][el_r[t]] = acc[t];
+    red_m.v[wave][el_c[t]][el_r[t]] = m[t];
+    red_s.v[wave][el_c[t]][el_r[t]] = acc[t];
   }
   __syncthreads();
   const int v = v0 + lane;
@@ -127,17 +132,265 @@ __global__ __launch_bounds__(256) void colscore_kernel(const uint16_t* __restric
     if (ROWS) {
       double mm = -INFINITY;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) mm = fmax(mm, red_m[wave][lane][r]);
+      for (int r = 0; r < 16; ++r) mm = fmax(mm, red_m.v[wave][lane][r]);
       double ss = 0.0;
 #pragma unroll
       for (int r = 0; r < 16; ++r)
-        if (red_s[wave][lane][r] > 0.0) ss += red_s[wave][lane][r] * exp(red_m[wave][lane][r] - mm);
+        if (red_s.v[wave][lane][r] > 0.0) ss += red_s.v[wave][lane][r] * exp(red_m.v[wave][lane][r] - mm);
       lse_bh[v] = mm + log(ss);
     } else {
       double ss = 0.0;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) ss += red_s[wave][lane][r];
-      col_key[((int64_t)b * H + h) * N + v] = (float)ss;
+      for (int r = 0; r < 16; ++r) ss += red_s.v[wave][lane][r];
+      col_bh[v] = (float)ss;
+    }
+  }
+  __syncthreads();
+}
+
+constexpr int kCsStage = 4;               // 16-vector blocks staged per step
+
+// Digits of the queries (side 0) and keys (side 1) of n_seg (batch, head) pairs from seg0 on, in the order in which
+// the statistic's waves take them: per 16-vector block, digit 3 .. 0, 64 dims and lane, 16 bytes.
+struct CsArgs {
+  const uint16_t *q, *k;
+  int N, H, seg0, n_seg, nblk;            // nblk = ceil(N / 16)
+  double sigma;
+  double* lse;                            // [n_seg, lse_stride]; log2 of the row sums where the digits serve
+  int64_t lse_stride;
+  float* col_key;                         // [B, H, N]
+  uint4* dig;                             // [2, n_seg, nblk, 4 D / 64, 64]; NULL: no workspace for digits
+  int* exps;                              // [2, n_seg, nblk4]: E - 30 of each block, nblk4 = nblk rounded up to 4
+  DigitStat* stat;                        // [2, n_seg, nblk]
+};
+
+template <int D>
+__global__ __launch_bounds__(256) void cs_digits_kernel(CsArgs a) {
+  constexpr int KS = D / 64;
+  const int lane = threadIdx.x & 63, blk = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int seg = blockIdx.y, side = blockIdx.z;
+  if (blk >= a.nblk) return;
+  const int b = (a.seg0 + seg) / a.H, h = (a.seg0 + seg) % a.H;
+  const int v = blk * 16 + (lane & 15);
+  uint4 w[2 * KS];
+#pragma unroll
+  for (int x = 0; x < 2 * KS; ++x) w[x] = make_uint4(0, 0, 0, 0);
+  if (v < a.N) {
+    const uint16_t* src = (side ? a.k : a.q) + (((int64_t)b * a.N + v) * a.H + h) * D + 16 * (lane >> 4);
+#pragma unroll
+    for (int x = 0; x < 2 * KS; ++x) w[x] = *reinterpret_cast<const uint4*>(src + 64 * (x >> 1) + 8 * (x & 1));
+  }
+  DigitStat stat;
+  const DigitBlock<D> o = make_digits<D>(w, stat);
+  const int64_t sb = ((int64_t)side * a.n_seg + seg) * a.nblk + blk;
+  i32x4* out = reinterpret_cast<i32x4*>(a.dig) + sb * (4 * KS * 64) + lane;
+#pragma unroll
+  for (int s = 0; s < 4; ++s)
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) out[(s * KS + ks) * 64] = o.d[s][ks];
+  if (lane == 0) {
+    a.stat[sb] = stat;
+    a.exps[((int64_t)side * a.n_seg + seg) * ((a.nblk + 3) & ~3) + blk] = stat.e - 30;
+  }
+}
+
+// largest of the blocks' figures of one side over the workgroup
+__device__ __forceinline__ DigitStat cs_side_stat(const DigitStat* __restrict__ st, int nblk, float (*red)[4]) {
+  DigitStat m = {0.0f, 0.0f, 0.0f, 0};
+  for (int x = threadIdx.x; x < nblk; x += 256) {
+    const DigitStat s = st[x];
+    m.res = fmaxf(m.res, s.res);
+    m.top = fmaxf(m.top, s.top);
+    m.norm = fmaxf(m.norm, s.norm);
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) {
+    m.res = fmaxf(m.res, __shfl_xor(m.res, off, 64));
+    m.top = fmaxf(m.top, __shfl_xor(m.top, off, 64));
+    m.norm = fmaxf(m.norm, __shfl_xor(m.norm, off, 64));
+  }
+  const int wave = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 0) { red[wave][0] = m.res; red[wave][1] = m.top; red[wave][2] = m.norm; }
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    m.res = fmaxf(m.res, red[w][0]);
+    m.top = fmaxf(m.top, red[w][1]);
+    m.norm = fmaxf(m.norm, red[w][2]);
+  }
+  __syncthreads();
+  return m;
+}
+
+// One stage of the other side: kCsStage blocks of digits, their exponents and (pass 2) the rows' log2 sums.
+template <int D>
+struct __attribute__((aligned(16))) CsSlot {
+  uint4 dig[kCsStage * 4 * (D / 64) * 64];
+  double lse[kCsStage * 16];
+  int exps[kCsStage];
+};
+
+// Dense column statistic in two passes over the digits.  A wave owns NB blocks of 16 vectors of one side in
+// registers, a workgroup 64 NB of them; the other side streams through two LDS slots, filled by LDS-DMA in the
+// order in which the waves read it (no bank conflicts, no shuffles).
+//   pass 1 (ROWS)  : own query rows against staged K columns j <= i: lse2_i = log2 sum 2^(l2_ij);
+//   pass 2 (!ROWS) : own K columns against staged query rows i >= j: col_j = sum 2^(l2_ij - lse2_i),
+// l2 = log2(e) l.  Exponents are bounded (digits_serve), so no running maximum is kept.
+// Bound by issue on both pipes: per 16 x 16 block and wave, 26 i8 products (416 matrix cycles) and about 95 vector
+// instructions (380 cycles) at d = 128, so the products of one block are issued between the exponentials of the
+// one before.  At N = 8192, 16 heads x 128: 0.73 ms a pass (11.5 -> 1.43 ms for the statistic and its lists; the fp64
+// products took 5.5 ms a pass), vector ALU 70 % and matrix cores 61 % of the busy cycles at 1.97 GHz.  Nine products
+// and a branch to four more where a digit 0 is present measured 0.95 ms: the branch ends the interleaving.
+template <int D, int NB, bool ROWS>
+__global__ __launch_bounds__(256, 2) void colscore_kernel(CsArgs a, int n_wg) {
+  constexpr int KS = D / 64;
+  constexpr int BLK = 4 * KS * 64;        // 16-byte pieces of a block
+  constexpr size_t kSlot = sizeof(CsSlot<D>) > sizeof(CsWide<D>) ? sizeof(CsSlot<D>) : sizeof(CsWide<D>);
+  static_assert(sizeof(CsMerge) <= sizeof(CsSlot<D>), "the wide path's merge buffers reuse the slots");
+  __shared__ __attribute__((aligned(16))) char slot0[kSlot];
+  __shared__ __attribute__((aligned(16))) char slot1[sizeof(CsSlot<D>)];
+  __shared__ float red[4][4];
+  // the workgroups of one (batch, head) go to one XCD (its digits stay in that L2), the longest ranges first
+  const int id = blockIdx.x;
+  int seg, rank;
+  if (a.n_seg % 8 == 0) {
+    const int per = a.n_seg / 8;
+    seg = (id & 7) + 8 * ((id >> 3) % per);
+    rank = (id >> 3) / per;
+  } else {
+    seg = id % a.n_seg;
+    rank = id / a.n_seg;
+  }
+  const int wg = ROWS ? n_wg - 1 - rank : rank;
+  const int gs = a.seg0 + seg;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  double* lse = a.lse + seg * a.lse_stride;
+  float* col = a.col_key + (int64_t)gs * a.N;
+  bool serve = a.dig != nullptr;
+  if (serve) {
+    const DigitStat sq = cs_side_stat(a.stat + (int64_t)seg * a.nblk, a.nblk, red);
+    const DigitStat sk = cs_side_stat(a.stat + ((int64_t)a.n_seg + seg) * a.nblk, a.nblk, red);
+    serve = digits_serve(sq, sk, D, a.sigma);
+  }
+  if (!serve) {                           // uniform
+    const int64_t base = (int64_t)(gs / a.H) * a.N * a.H * D + (int64_t)(gs % a.H) * D;
+    for (int x = 0; x < NB; ++x)
+      if ((wg * NB + x) * 64 < a.N)
+        colscore_wide<D, ROWS>(a.q + base, a.k + base, a.N, a.H, a.sigma, lse, col, (wg * NB + x) * 64,
+                               *reinterpret_cast<CsWide<D>*>(slot0), *reinterpret_cast<CsMerge*>(slot0),
+                               *reinterpret_cast<CsMerge*>(slot1));
+    return;
+  }
+  CsSlot<D>& s0 = *reinterpret_cast<CsSlot<D>*>(slot0);
+  CsSlot<D>& s1 = *reinterpret_cast<CsSlot<D>*>(slot1);
+  const int64_t own_side = (int64_t)(ROWS ? 0 : a.n_seg) + seg, oth_side = (int64_t)(ROWS ? a.n_seg : 0) + seg;
+  const int nblk4 = (a.nblk + 3) & ~3;
+  const int first = wg * NB * 4;          // first own block of the workgroup; block first + 4 nb + wave is the wave's
+  DigitBlock<D> own[NB];
+  double f_own[NB], acc[NB];
+  int ob[NB];
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    ob[nb] = first + 4 * nb + wave;
+    const int x = min(ob[nb], a.nblk - 1);
+    const i32x4* src = reinterpret_cast<const i32x4*>(a.dig) + (own_side * a.nblk + x) * BLK + lane;
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) own[nb].d[s][ks] = src[(s * KS + ks) * 64];
+    // sigma log2(e), the unit of digit_dot and the own block's exponent
+    f_own[nb] = __builtin_ldexp(a.sigma * 0x1.71547652b82fep+16, a.exps[own_side * nblk4 + x]);
+    acc[nb] = 0.0;
+  }
+  const int s_begin = ROWS ? 0 : first;
+  const int s_end = ROWS ? min(a.nblk, first + 4 * NB) : a.nblk;
+  const rsrc_t digR = make_rsrc(a.dig + oth_side * a.nblk * BLK, (uint32_t)a.nblk * BLK * 16u);
+  const rsrc_t expR = make_rsrc(a.exps + oth_side * nblk4, (uint32_t)nblk4 * 4u);
+  const rsrc_t lseR = make_rsrc(lse, (uint32_t)a.nblk * 128u);
+  auto fill = [&](CsSlot<D>& sl, int t0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int x = 0; x < kCsStage * 4 * KS / 4; ++x) {
+      const int piece = 4 * x + wave;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(digR, FL_LDS(sl.dig + piece * 64), 16,
+                                               (uint32_t)(t0 * BLK + piece * 64 + lane) * 16u, 0, 0, 0);
+    }
+    static_assert(kCsStage == 4, "a stage's exponents: 16 bytes; its log2 sums: 32 lanes of 16 bytes");
+    if (wave == 0 && lane < 1)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(expR, FL_LDS(sl.exps), 16, (uint32_t)t0 * 4u, 0, 0, 0);
+    if (!ROWS && wave == 1 && lane < 32)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(lseR, FL_LDS(sl.lse), 16, (uint32_t)t0 * 128u + lane * 16u, 0, 0, 0);
+  };
+  // the exponentials of one block, added to acc; edge: with the causal bound and the end of the rows
+  auto add = [&](const CsSlot<D>& sl, const DigitSums& o, int t0, int x, int nb, auto edge) __attribute__((always_inline)) {
+    const double f = __builtin_ldexp(f_own[nb], sl.exps[x]);
+    double e[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const double v = digit_dot(o, t);
+      double z = ROWS ? v * f : fma(v, f, -sl.lse[x * 16 + 4 * (lane >> 4) + t]);
+      if (edge.value) {
+        const int sv = (t0 + x) * 16 + 4 * (lane >> 4) + t, ov = ob[nb] * 16 + (lane & 15);
+        z = (ROWS ? sv <= ov : sv >= ov && sv < a.N) ? z : -1000.0;
+      }
+      e[t] = exp2_f64(z);
+    }
+    acc[nb] += (e[0] + e[1]) + (e[2] + e[3]);
+  };
+  auto load = [&](const CsSlot<D>& sl, int x, i32x4 (&d)[4][KS]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+        d[s][ks] = reinterpret_cast<const i32x4*>(sl.dig)[(x * 4 * KS + s * KS + ks) * 64 + lane];
+  };
+  // the stage's blocks against the own ones, the products of a block one block ahead of its exponentials
+  auto stage = [&](const CsSlot<D>& sl, int t0, auto edge) __attribute__((always_inline)) {
+    i32x4 d[4][KS];
+    DigitSums o[2];
+    load(sl, 0, d);
+    digit_sums<D>(d, own[0], o[0]);
+#pragma unroll
+    for (int i = 0; i < kCsStage * NB; ++i) {
+      if (i + 1 < kCsStage * NB) {
+        if ((i + 1) % NB == 0) load(sl, (i + 1) / NB, d);
+        digit_sums<D>(d, own[(i + 1) % NB], o[(i + 1) & 1]);
+      }
+      add(sl, o[i & 1], t0, i / NB, i % NB, edge);
+#pragma unroll
+      for (int y = 0; y < 13 * KS; ++y) {
+        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);              // a product, and the vector instructions
+        __builtin_amdgcn_sched_group_barrier(0x2, KS == 2 ? 4 : 7, 0);   // that its matrix cycles cover
+      }
+    }
+  };
+  auto work = [&](const CsSlot<D>& sl, int t0) __attribute__((always_inline)) {
+    if (ROWS ? t0 > ob[NB - 1] : t0 + kCsStage - 1 < ob[0]) return;       // nothing of it is visible
+    const bool full = ROWS ? t0 + kCsStage - 1 < ob[0] : t0 > ob[NB - 1] && (t0 + kCsStage) * 16 <= a.N;
+    if (full) stage(sl, t0, std::false_type{});
+    else stage(sl, t0, std::true_type{});
+  };
+  fill(s0, s_begin);
+  FL_WAIT_VM(0);
+  lds_barrier();
+  for (int t0 = s_begin; t0 < s_end; t0 += 2 * kCsStage) {
+    if (t0 + kCsStage < s_end) fill(s1, t0 + kCsStage);
+    work(s0, t0);
+    FL_WAIT_VM(0);
+    lds_barrier();
+    if (t0 + 2 * kCsStage < s_end) fill(s0, t0 + 2 * kCsStage);
+    if (t0 + kCsStage < s_end) work(s1, t0 + kCsStage);
+    FL_WAIT_VM(0);
+    lds_barrier();
+  }
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    double s = acc[nb];
+    s += __shfl_xor(s, 16, 64);
+    s += __shfl_xor(s, 32, 64);
+    const int v = ob[nb] * 16 + lane;
+    if (lane < 16 && ob[nb] < a.nblk) {
+      if (ROWS) lse[v] = v < a.N ? log2(s) : 0.0;
+      else if (v < a.N) col[v] = (float)s;
     }
   }
 }
@@ -275,9 +528,53 @@ __global__ __launch_bounds__(256) void prune_sum_kernel(const double* __restrict
 
 using namespace fl;
 
+// Workspace of the dense statistic: the rows' log-normalisers and digits of n_seg (batch, head) pairs at a time.
+// The digits take 4 bytes per element of q and of k, so the pairs go in groups of about 256 MB (a 32K prompt of 16
+// heads x 128 in two groups of 8).
+namespace {
+struct CsWs {
+  int n_seg;
+  size_t dig, exps, stat, total;
+};
+constexpr size_t kCsGroupBytes = (size_t)256 << 20;
+
+CsWs cs_ws(int B, int N, int H, int d) {
+  const size_t nblk = ((size_t)N + 15) / 16;
+  const size_t pair = 2 * nblk * 16 * (size_t)d * 4;
+  const size_t all = (size_t)B * H;
+  size_t n = kCsGroupBytes / pair;
+  n = n < 1 ? 1 : n > all ? all : n;
+  const size_t groups = (all + n - 1) / n;
+  n = (all + groups - 1) / groups;
+  if (n > 8 && n < all) n = (n + 7) / 8 * 8 <= kCsGroupBytes / pair ? (n + 7) / 8 * 8 : n / 8 * 8;
+  CsWs w;
+  w.n_seg = (int)n;
+  size_t off = n * nblk * 16 * sizeof(double);          // lse [n_seg, 16 nblk]
+  w.dig = off; off += n * pair;
+  w.exps = off; off += 2 * n * ((nblk + 3) / 4 * 4) * sizeof(int);
+  w.stat = off; off += 2 * n * nblk * sizeof(DigitStat);
+  w.total = off;
+  return w;
+}
+
+template <int D, int NB>
+int launch_colscore(const CsArgs& a, hipStream_t st) {
+  const int n_wg = (a.nblk + 4 * NB - 1) / (4 * NB);
+  const unsigned grid = (unsigned)n_wg * (unsigned)a.n_seg;
+  colscore_kernel<D, NB, true><<<grid, 256, 0, st>>>(a, n_wg);
+  int rc = check_launch("colscore_kernel(rows)");
+  if (rc != FL_OK) return rc;
+  colscore_kernel<D, NB, false><<<grid, 256, 0, st>>>(a, n_wg);
+  return check_launch("colscore_kernel(columns)");
+}
+}  // namespace
+
+// (the head dimension is not an argument: sized for 128)
 extern "C" size_t fl_column_scores_ws(int B, int N, int H) {
   if (B < 1 || N < 1 || H < 1) return 0;
-  return (size_t)B * (size_t)H * (size_t)N * sizeof(double);
+  const size_t rows = (size_t)B * (size_t)H * (size_t)N * sizeof(double);
+  const size_t digits = cs_ws(B, N, H, 128).total;
+  return digits > rows ? digits : rows;
 }
 
 extern "C" int fl_column_scores(const uint16_t* q, const uint16_t* k_cache, int B, int N, int H, int d,
@@ -287,24 +584,49 @@ extern "C" int fl_column_scores(const uint16_t* q, const uint16_t* k_cache, int 
   FL_REQUIRE(B >= 1 && N >= 1 && H >= 1, FL_E_SHAPE, "fl_column_scores: need B, N, H >= 1");
   FL_REQUIRE(d == 64 || d == 128, FL_E_SHAPE, "fl_column_scores: head dim %d not in {64, 128}", d);
   FL_REQUIRE((int64_t)N * H * d < ((int64_t)1 << 31), FL_E_SHAPE, "fl_column_scores: N * H * d too large");
-  FL_REQUIRE(ws && ws_bytes >= fl_column_scores_ws(B, N, H), FL_E_WORKSPACE,
-             "fl_column_scores: workspace of %zu bytes required", fl_column_scores_ws(B, N, H));
+  // (the rows' log-normalisers alone are the least a call can work with)
+  const size_t least = (size_t)B * (size_t)H * (size_t)N * sizeof(double);
+  FL_REQUIRE(ws && ws_bytes >= least, FL_E_WORKSPACE, "fl_column_scores: workspace of %zu bytes required", least);
   hipStream_t st = as_stream(stream);
-  const double sigma = 1.0 / std::sqrt((double)d);
-  double* lse = static_cast<double*>(ws);
-  dim3 grid((N + 63) / 64, H, B);
-  if (d == 128) {
-    colscore_kernel<128, true><<<grid, 256, 0, st>>>(q, k_cache, N, H, sigma, lse, col_key);
-    int rc = check_launch("colscore_kernel(rows)");
-    if (rc != FL_OK) return rc;
-    colscore_kernel<128, false><<<grid, 256, 0, st>>>(q, k_cache, N, H, sigma, lse, col_key);
-  } else {
-    colscore_kernel<64, true><<<grid, 256, 0, st>>>(q, k_cache, N, H, sigma, lse, col_key);
-    int rc = check_launch("colscore_kernel(rows)");
-    if (rc != FL_OK) return rc;
-    colscore_kernel<64, false><<<grid, 256, 0, st>>>(q, k_cache, N, H, sigma, lse, col_key);
+  CsArgs a{};
+  a.q = q; a.k = k_cache; a.N = N; a.H = H; a.nblk = (N + 15) / 16;
+  a.sigma = 1.0 / std::sqrt((double)d);
+  a.col_key = col_key;
+  a.lse = static_cast<double*>(ws);
+  const CsWs w = cs_ws(B, N, H, d);
+  // The digits: with the workspace that fl_column_scores_ws asks for, 16-byte aligned queries and keys, and digits of
+  // one pair within a buffer descriptor's 2 GiB; otherwise every pair takes the fp64 products.
+  const bool aligned = ((reinterpret_cast<uintptr_t>(q) | reinterpret_cast<uintptr_t>(k_cache) | reinterpret_cast<uintptr_t>(ws)) & 15) == 0;
+  const bool digits = aligned && ws_bytes >= w.total && (int64_t)a.nblk * 64 * d < ((int64_t)1 << 31);
+  const int all = B * H;
+  int step = all;
+  a.lse_stride = N;
+  if (digits) {
+    char* base = static_cast<char*>(ws);
+    a.dig = reinterpret_cast<uint4*>(base + w.dig);
+    a.exps = reinterpret_cast<int*>(base + w.exps);
+    a.stat = reinterpret_cast<DigitStat*>(base + w.stat);
+    a.lse_stride = (int64_t)a.nblk * 16;
+    step = w.n_seg;
   }
-  return check_launch("colscore_kernel(columns)");
+  for (int s0 = 0; s0 < all; s0 += step) {
+    a.seg0 = s0;
+    a.n_seg = std::min(step, all - s0);
+    if (digits) {
+      const dim3 grid((a.nblk + 3) / 4, a.n_seg, 2);
+      if (d == 128) cs_digits_kernel<128><<<grid, 256, 0, st>>>(a);
+      else cs_digits_kernel<64><<<grid, 256, 0, st>>>(a);
+      int rc = check_launch("cs_digits_kernel");
+      if (rc != FL_OK) return rc;
+    }
+    // two blocks per wave halve the reads of the staged digits; one where that leaves less than two workgroups per CU
+    const bool wide = (int64_t)((a.nblk + 7) / 8) * a.n_seg >= 512;
+    int rc;
+    if (d == 128) rc = wide ? launch_colscore<128, 2>(a, st) : launch_colscore<128, 1>(a, st);
+    else rc = wide ? launch_colscore<64, 2>(a, st) : launch_colscore<64, 1>(a, st);
+    if (rc != FL_OK) return rc;
+  }
+  return FL_OK;
   FL_API_END
 }
 

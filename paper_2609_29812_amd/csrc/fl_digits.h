@@ -1,0 +1,191 @@
+// Dot products of bf16 vectors as integer sums on the i8 matrix instructions, for the fp64 statistics.
+//
+// Sixteen vectors with max|x| < 2^E are taken as integers X_e = rint(x_e 2^(30 - E)), |X| <= 2^30, and X as four
+// balanced base-256 digits: X = sum_s d_s 256^s, d_s in [-128, 127] (|d_3| <= 64).  A bf16 value has 8 significant
+// bits, so X_e is exact unless 0 < |x_e| < 2^(E - 22).  The dot product is the sum over digit pairs (s, t) of
+// 256^(s + t) sum_e d_s d'_t, each inner sum exact in int32, and pairs of one weight share an accumulator.  The
+// pairs of weight 256 and 1 (a digit 0, which only elements below 2^(E - 14) have, with a digit 1 or 0) are left out:
+// at most 2^-36 of 2^E 2^E' for an element, counted in digits_serve.
+//
+// Thirteen 8-bit products at twice the bf16 rate replace the fp64 product at 1/32 of it (2.5 PFLOP/s against
+// 78.6 TFLOP/s): about 5 times the rate of the fp64 matrix instructions for the same sums.
+#pragma once
+#include "fl_common.h"
+
+namespace fl {
+
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+
+// What 16 vectors hold: the largest sum over one vector of the absolute values that the digits leave out, the bound
+// of their elements (2^E; +inf if one is not finite) and their largest 2-norm.
+struct DigitStat {
+  float res, top, norm;
+  int e;                    // E
+};
+
+// Digits of 8 consecutive elements per uint4 of bf16 pairs: out[s][0..1] = digit s of elements 0-3 and 4-7.
+__device__ __forceinline__ void digits8(uint4 w, float scale, uint32_t (&out)[4][2], float& res) {
+  const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
+  uint32_t y[8];
+#pragma unroll
+  for (int t = 0; t < 8; ++t) {
+    const float v = bf16_to_f32((t & 1) ? ws[t >> 1] >> 16 : ws[t >> 1] & 0xFFFFu) * scale;   // a power of two
+    const float n = rintf(v);
+    res += fabsf(v - n);
+    // X + 0x80808080 has the bytes d_s + 128, and flipping their high bits gives d_s
+    y[t] = ((uint32_t)(int)n + 0x80808080u) ^ 0x80808080u;
+  }
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {             // 4 x 4 byte transpose
+    const uint32_t lo01 = __builtin_amdgcn_perm(y[4 * q + 1], y[4 * q], 0x05010400u);   // d0 d0 d1 d1
+    const uint32_t lo23 = __builtin_amdgcn_perm(y[4 * q + 3], y[4 * q + 2], 0x05010400u);
+    const uint32_t hi01 = __builtin_amdgcn_perm(y[4 * q + 1], y[4 * q], 0x07030602u);   // d2 d2 d3 d3
+    const uint32_t hi23 = __builtin_amdgcn_perm(y[4 * q + 3], y[4 * q + 2], 0x07030602u);
+    out[0][q] = __builtin_amdgcn_perm(lo23, lo01, 0x05040100u);
+    out[1][q] = __builtin_amdgcn_perm(lo23, lo01, 0x07060302u);
+    out[2][q] = __builtin_amdgcn_perm(hi23, hi01, 0x05040100u);
+    out[3][q] = __builtin_amdgcn_perm(hi23, hi01, 0x07060302u);
+  }
+}
+
+__device__ __forceinline__ uint32_t max_abs_bits(uint4 w, uint32_t m) {
+  const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+  for (int t = 0; t < 4; ++t) m = max(m, max(ws[t] & 0x7FFFu, (ws[t] >> 16) & 0x7FFFu));
+  return m;
+}
+
+// E of a vector whose largest |bf16| pattern is m, kept where the scale 2^(30 - E) is a normal float; 129 for
+// infinities and NaN.
+__device__ __forceinline__ int digit_exponent(uint32_t m) { return max((int)(m >> 7) - 126, -90); }
+__device__ __forceinline__ float digit_scale(int e) { return __uint_as_float((uint32_t)(157 - e) << 23); }   // 2^(30 - e)
+
+// Digits of 16 vectors as one wave holds them: lane (l16, g) = (lane % 16, lane / 16) holds dims 64 ks + 16 g ..
+// + 15 of vector l16 (any split of the dims over g serves, being the same on both sides of a product).
+// d[s][ks] is the lane's operand of v_mfma_i32_16x16x64_i8 for digit 3 - s.
+template <int D>
+struct DigitBlock {
+  i32x4 d[4][D / 64];
+};
+
+// w: the lane's 2 KS loads of 8 elements.  stat: of the 16 vectors, the same in every lane.
+template <int D>
+__device__ __forceinline__ DigitBlock<D> make_digits(const uint4 (&w)[2 * (D / 64)], DigitStat& stat) {
+  constexpr int KS = D / 64;
+  DigitBlock<D> o;
+  uint32_t m = 0;
+#pragma unroll
+  for (int x = 0; x < 2 * KS; ++x) m = max_abs_bits(w[x], m);
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off, 64));
+  const int e = digit_exponent(m);
+  const bool finite = m < 0x7F80u;
+  const float scale = digit_scale(e);
+  float res = 0.0f, n2 = 0.0f;
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) {
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      uint32_t q[4][2];
+      digits8(w[2 * ks + half], scale, q, res);
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        o.d[s][ks][2 * half] = (int)q[3 - s][0];
+        o.d[s][ks][2 * half + 1] = (int)q[3 - s][1];
+      }
+      const uint32_t ws[4] = {w[2 * ks + half].x, w[2 * ks + half].y, w[2 * ks + half].z, w[2 * ks + half].w};
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const float a = bf16_to_f32(ws[t] & 0xFFFFu), c = bf16_to_f32(ws[t] >> 16);
+        n2 = fmaf(a, a, fmaf(c, c, n2));
+      }
+    }
+  }
+  const float unit = __uint_as_float((uint32_t)max(e - 30 + 127, 1) << 23);     // 2^(e - 30), at least 2^-126
+  res += __shfl_xor(res, 16, 64);
+  res += __shfl_xor(res, 32, 64);
+  n2 += __shfl_xor(n2, 16, 64);
+  n2 += __shfl_xor(n2, 32, 64);
+  float norm = sqrtf(n2);
+#pragma unroll
+  for (int off = 1; off < 16; off <<= 1) {
+    res = fmaxf(res, __shfl_xor(res, off, 64));
+    norm = fmaxf(norm, __shfl_xor(norm, off, 64));
+  }
+  stat.res = finite ? res * unit : INFINITY;
+  stat.top = finite ? unit * 0x1p30f : INFINITY;
+  stat.norm = finite ? norm : INFINITY;
+  stat.e = e;
+  return o;
+}
+
+// Whether the digits serve all dot products between the vectors of two sides: with `scale` the factor from dot
+// product to natural exponent, what the digits leave out moves an exponent by at most 2^-24 (half an ulp of the
+// fp32 results), and no exponent leaves +-330 (its base-2 form stays far inside the doubles' range without a running
+// maximum).  False for infinities and NaN.
+__device__ __forceinline__ bool digits_serve(const DigitStat& a, const DigitStat& b, int d, double scale) {
+  // the products left out: |d_0 d'_1 256 + d_1 d'_0 256 + d_0 d'_0| <= 2^23.01 per element, in units of
+  // 2^(E + E' - 60); rare where the elements are not all tiny, and bounded here as if every one had them
+  const double pairs = d * 0x1.02p-37 * (double)a.top * b.top;
+  const double off = ((double)a.res * b.top + (double)b.res * a.top + pairs) * scale;
+  const double most = (double)a.norm * b.norm * scale;
+  return off <= 0x1p-24 && most <= 330.0;
+}
+
+// Integer sums of a 16 x 16 block of dot products (rows 4 g + t of `a`, column l16 of `b`), by weight 256^(n + 2).
+struct DigitSums {
+  i32x4 s[5];
+};
+
+template <int D>
+__device__ __forceinline__ void digit_sums(const i32x4 (&a)[4][D / 64], const DigitBlock<D>& b, DigitSums& o) {
+  i32x4 s6 = {0, 0, 0, 0}, s5 = s6, s4 = s6, s3 = s6, s2 = s6;
+#define FL_DIG(acc, x, y) acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[3 - (x)][ks], b.d[3 - (y)][ks], acc, 0, 0, 0)
+#pragma unroll
+  for (int ks = 0; ks < D / 64; ++ks) {
+    FL_DIG(s6, 3, 3);
+    FL_DIG(s5, 3, 2);
+    FL_DIG(s4, 3, 1);
+    FL_DIG(s3, 3, 0);
+    FL_DIG(s2, 2, 0);
+    FL_DIG(s5, 2, 3);
+    FL_DIG(s4, 2, 2);
+    FL_DIG(s3, 2, 1);
+    FL_DIG(s2, 1, 1);
+    FL_DIG(s4, 1, 3);
+    FL_DIG(s3, 1, 2);
+    FL_DIG(s2, 0, 2);
+    FL_DIG(s3, 0, 3);
+  }
+#undef FL_DIG
+  o.s[0] = s2; o.s[1] = s3; o.s[2] = s4; o.s[3] = s5; o.s[4] = s6;
+}
+
+// The lane's dot product t in units of 2^16 2^(E + E' - 60).  |s6| <= 2^19, |s4| < 2^22 and |s3| < 2^23 for 128
+// dims, so each shifted pair fits int32; the doubles hold the sum exactly (below 2^52).
+__device__ __forceinline__ double digit_dot(const DigitSums& o, int t) {
+  const double p = fma((double)(o.s[4][t] * 256 + o.s[3][t]), 65536.0, (double)(o.s[2][t] * 256 + o.s[1][t]));
+  return fma(p, 256.0, (double)o.s[0][t]);
+}
+
+// 2^x for |x| <= 1000: 2^rint(x) times a degree-10 polynomial of the rest (the Chebyshev interpolant of 2^r on
+// [-1/2, 1/2]; relative error below 4e-16 before rounding).
+__device__ __forceinline__ double exp2_f64(double x) {
+  const double big = 0x1.8p52;
+  const double y = x + big;                    // the low word of y is the nearest integer to x
+  const double r = x - (y - big);
+  double p = 0x1.e606343d16a96p-28;
+  p = fma(p, r, 0x1.b675bc52c98b0p-24);
+  p = fma(p, r, 0x1.62bfd47ecba29p-20);
+  p = fma(p, r, 0x1.ffcb540682f51p-17);
+  p = fma(p, r, 0x1.430913096c64ap-13);
+  p = fma(p, r, 0x1.5d87fe9d7a3b5p-10);
+  p = fma(p, r, 0x1.3b2ab6fba1defp-7);
+  p = fma(p, r, 0x1.c6b08d703ce4ap-5);
+  p = fma(p, r, 0x1.ebfbdff82c598p-3);
+  p = fma(p, r, 0x1.62e42fefa3a19p-1);
+  p = fma(p, r, 1.0);
+  return __builtin_ldexp(p, (int)(uint32_t)__double_as_longlong(y));
+}
+
+}  // namespace fl
