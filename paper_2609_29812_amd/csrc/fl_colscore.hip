@@ -4,9 +4,8 @@
 //     over the rows of a prefill), in two passes: the rows' log-normalisers, then the column sums;
 //   * the statistic that prunes a list for a smaller budget (Section 4.2): the mass the updated rows give
 //     each list entry, from their stored reference log-normalisers.
-// The dense statistic's dot products are integer products of byte digits (fl_digits.h), or v_mfma_f64_16x16x4
-// products (products of bf16 values are exact in fp64) where the digits do not hold the values; the list
-// statistic's are the latter.  Every sum runs in a fixed order (deterministic).
+// The dot products are integer products of byte digits (fl_digits.h), or v_mfma_f64_16x16x4 products (products of bf16
+// values are exact in fp64) where the digits do not hold the values.  Every sum runs in a fixed order (deterministic).
 #include "fl_attn_util.h"
 #include "fl_digits.h"
 
@@ -148,8 +147,6 @@ __device__ __forceinline__ void colscore_wide(const uint16_t* __restrict__ qbase
   __syncthreads();
 }
 
-constexpr int kCsStage = 4;               // 16-vector blocks staged per step
-
 // Digits of the queries (side 0) and keys (side 1) of n_seg (batch, head) pairs from seg0 on, in the order in which
 // the statistic's waves take them: per 16-vector block, digit 3 .. 0, 64 dims and lane, 16 bytes.
 struct CsArgs {
@@ -222,12 +219,12 @@ __device__ __forceinline__ DigitStat cs_side_stat(const DigitStat* __restrict__ 
   return m;
 }
 
-// One stage of the other side: kCsStage blocks of digits, their exponents and (pass 2) the rows' log2 sums.
-template <int D>
+// One stage of the other side: STG blocks of digits, their exponents and (pass 2) the rows' log2 sums.
+template <int D, int STG>
 struct __attribute__((aligned(16))) CsSlot {
-  uint4 dig[kCsStage * 4 * (D / 64) * 64];
-  double lse[kCsStage * 16];
-  int exps[kCsStage];
+  uint4 dig[STG * 4 * (D / 64) * 64];
+  double lse[STG * 16];
+  int exps[STG];
 };
 
 // Dense column statistic in two passes over the digits.  A wave owns NB blocks of 16 vectors of one side in
@@ -242,13 +239,13 @@ struct __attribute__((aligned(16))) CsSlot {
 // products took 5.5 ms a pass), vector ALU 70 % and matrix cores 61 % of the busy cycles at 1.97 GHz.  Nine products
 // and a branch to four more where a digit 0 is present measured 0.95 ms: the branch ends the interleaving.
 template <int D, int NB, bool ROWS>
-__global__ __launch_bounds__(256, 2) void colscore_kernel(CsArgs a, int n_wg) {
-  constexpr int KS = D / 64;
+__global__ __launch_bounds__(256, NB == 1 ? 3 : 2) void colscore_kernel(CsArgs a, int n_wg) {
+  constexpr int KS = D / 64, STG = NB == 1 ? 2 : 4;
   constexpr int BLK = 4 * KS * 64;        // 16-byte pieces of a block
-  constexpr size_t kSlot = sizeof(CsSlot<D>) > sizeof(CsWide<D>) ? sizeof(CsSlot<D>) : sizeof(CsWide<D>);
-  static_assert(sizeof(CsMerge) <= sizeof(CsSlot<D>), "the wide path's merge buffers reuse the slots");
+  constexpr size_t kSlot = sizeof(CsSlot<D, STG>) > sizeof(CsWide<D>) ? sizeof(CsSlot<D, STG>) : sizeof(CsWide<D>);
+  constexpr size_t kSlot1 = sizeof(CsSlot<D, STG>) > sizeof(CsMerge) ? sizeof(CsSlot<D, STG>) : sizeof(CsMerge);
   __shared__ __attribute__((aligned(16))) char slot0[kSlot];
-  __shared__ __attribute__((aligned(16))) char slot1[sizeof(CsSlot<D>)];
+  __shared__ __attribute__((aligned(16))) char slot1[kSlot1];
   __shared__ float red[4][4];
   // the workgroups of one (batch, head) go to one XCD (its digits stay in that L2), the longest ranges first
   const int id = blockIdx.x;
@@ -281,8 +278,8 @@ __global__ __launch_bounds__(256, 2) void colscore_kernel(CsArgs a, int n_wg) {
                                *reinterpret_cast<CsMerge*>(slot1));
     return;
   }
-  CsSlot<D>& s0 = *reinterpret_cast<CsSlot<D>*>(slot0);
-  CsSlot<D>& s1 = *reinterpret_cast<CsSlot<D>*>(slot1);
+  CsSlot<D, STG>& s0 = *reinterpret_cast<CsSlot<D, STG>*>(slot0);
+  CsSlot<D, STG>& s1 = *reinterpret_cast<CsSlot<D, STG>*>(slot1);
   const int64_t own_side = (int64_t)(ROWS ? 0 : a.n_seg) + seg, oth_side = (int64_t)(ROWS ? a.n_seg : 0) + seg;
   const int nblk4 = (a.nblk + 3) & ~3;
   const int first = wg * NB * 4;          // first own block of the workgroup; block first + 4 nb + wave is the wave's
@@ -307,21 +304,20 @@ __global__ __launch_bounds__(256, 2) void colscore_kernel(CsArgs a, int n_wg) {
   const rsrc_t digR = make_rsrc(a.dig + oth_side * a.nblk * BLK, (uint32_t)a.nblk * BLK * 16u);
   const rsrc_t expR = make_rsrc(a.exps + oth_side * nblk4, (uint32_t)nblk4 * 4u);
   const rsrc_t lseR = make_rsrc(lse, (uint32_t)a.nblk * 128u);
-  auto fill = [&](CsSlot<D>& sl, int t0) __attribute__((always_inline)) {
+  auto fill = [&](CsSlot<D, STG>& sl, int t0) __attribute__((always_inline)) {
 #pragma unroll
-    for (int x = 0; x < kCsStage * 4 * KS / 4; ++x) {
+    for (int x = 0; x < STG * 4 * KS / 4; ++x) {
       const int piece = 4 * x + wave;
       __builtin_amdgcn_raw_ptr_buffer_load_lds(digR, FL_LDS(sl.dig + piece * 64), 16,
                                                (uint32_t)(t0 * BLK + piece * 64 + lane) * 16u, 0, 0, 0);
     }
-    static_assert(kCsStage == 4, "a stage's exponents: 16 bytes; its log2 sums: 32 lanes of 16 bytes");
-    if (wave == 0 && lane < 1)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(expR, FL_LDS(sl.exps), 16, (uint32_t)t0 * 4u, 0, 0, 0);
-    if (!ROWS && wave == 1 && lane < 32)
+    if (wave == 0 && lane < STG)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(expR, FL_LDS(sl.exps), 4, (uint32_t)(t0 + lane) * 4u, 0, 0, 0);
+    if (!ROWS && wave == 1 && lane < STG * 8)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(lseR, FL_LDS(sl.lse), 16, (uint32_t)t0 * 128u + lane * 16u, 0, 0, 0);
   };
   // the exponentials of one block, added to acc; edge: with the causal bound and the end of the rows
-  auto add = [&](const CsSlot<D>& sl, const DigitSums& o, int t0, int x, int nb, auto edge) __attribute__((always_inline)) {
+  auto add = [&](const CsSlot<D, STG>& sl, const DigitSums& o, int t0, int x, int nb, auto edge) __attribute__((always_inline)) {
     const double f = __builtin_ldexp(f_own[nb], sl.exps[x]);
     double e[4];
 #pragma unroll
@@ -336,49 +332,27 @@ __global__ __launch_bounds__(256, 2) void colscore_kernel(CsArgs a, int n_wg) {
     }
     acc[nb] += (e[0] + e[1]) + (e[2] + e[3]);
   };
-  auto load = [&](const CsSlot<D>& sl, int x, i32x4 (&d)[4][KS]) __attribute__((always_inline)) {
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
-        d[s][ks] = reinterpret_cast<const i32x4*>(sl.dig)[(x * 4 * KS + s * KS + ks) * 64 + lane];
+  auto stage = [&](const CsSlot<D, STG>& sl, int t0, auto edge) __attribute__((always_inline)) {
+    digit_stage<D, NB, STG>(sl.dig, own, [&](const DigitSums& o, int x, int nb) __attribute__((always_inline)) {
+      add(sl, o, t0, x, nb, edge);
+    });
   };
-  // the stage's blocks against the own ones, the products of a block one block ahead of its exponentials
-  auto stage = [&](const CsSlot<D>& sl, int t0, auto edge) __attribute__((always_inline)) {
-    i32x4 d[4][KS];
-    DigitSums o[2];
-    load(sl, 0, d);
-    digit_sums<D>(d, own[0], o[0]);
-#pragma unroll
-    for (int i = 0; i < kCsStage * NB; ++i) {
-      if (i + 1 < kCsStage * NB) {
-        if ((i + 1) % NB == 0) load(sl, (i + 1) / NB, d);
-        digit_sums<D>(d, own[(i + 1) % NB], o[(i + 1) & 1]);
-      }
-      add(sl, o[i & 1], t0, i / NB, i % NB, edge);
-#pragma unroll
-      for (int y = 0; y < 13 * KS; ++y) {
-        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);              // a product, and the vector instructions
-        __builtin_amdgcn_sched_group_barrier(0x2, KS == 2 ? 4 : 7, 0);   // that its matrix cycles cover
-      }
-    }
-  };
-  auto work = [&](const CsSlot<D>& sl, int t0) __attribute__((always_inline)) {
-    if (ROWS ? t0 > ob[NB - 1] : t0 + kCsStage - 1 < ob[0]) return;       // nothing of it is visible
-    const bool full = ROWS ? t0 + kCsStage - 1 < ob[0] : t0 > ob[NB - 1] && (t0 + kCsStage) * 16 <= a.N;
+  auto work = [&](const CsSlot<D, STG>& sl, int t0) __attribute__((always_inline)) {
+    if (ROWS ? t0 > ob[NB - 1] : t0 + STG - 1 < ob[0]) return;       // nothing of it is visible
+    const bool full = ROWS ? t0 + STG - 1 < ob[0] : t0 > ob[NB - 1] && (t0 + STG) * 16 <= a.N;
     if (full) stage(sl, t0, std::false_type{});
     else stage(sl, t0, std::true_type{});
   };
   fill(s0, s_begin);
   FL_WAIT_VM(0);
   lds_barrier();
-  for (int t0 = s_begin; t0 < s_end; t0 += 2 * kCsStage) {
-    if (t0 + kCsStage < s_end) fill(s1, t0 + kCsStage);
+  for (int t0 = s_begin; t0 < s_end; t0 += 2 * STG) {
+    if (t0 + STG < s_end) fill(s1, t0 + STG);
     work(s0, t0);
     FL_WAIT_VM(0);
     lds_barrier();
-    if (t0 + 2 * kCsStage < s_end) fill(s0, t0 + 2 * kCsStage);
-    if (t0 + kCsStage < s_end) work(s1, t0 + kCsStage);
+    if (t0 + 2 * STG < s_end) fill(s0, t0 + 2 * STG);
+    if (t0 + STG < s_end) work(s1, t0 + STG);
     FL_WAIT_VM(0);
     lds_barrier();
   }
@@ -398,54 +372,59 @@ __global__ __launch_bounds__(256, 2) void colscore_kernel(CsArgs a, int n_wg) {
 // Statistic of the list entries for pruning a shrinking list (Section 4.2; Appendix D.2, Eq. 6 with a
 // sparse source): entry j of the (b, h) list gets sum_{i updated, i >= j} exp(sigma q_i . k_j - lse_ref_i),
 // the loop-r probability mass it receives from the updated rows, each row's probabilities recovered from
-// its reference log-normaliser.  The dot products are fp64 MFMAs (v_mfma_f64_16x16x4): a wave owns 16
-// entries (their K rows as the B operand, in registers: lane l holds dim 4s + l / 16 of entry l % 16 for
-// step s), a workgroup 64 entries and one chunk of kPruneChunk updated rows, staged 32 rows at a time in
-// LDS as fp64 (the A operand: row l % 16, dim 4s + l / 16).  Which accumulator element is which (row,
-// entry) is read off two index products at the start, so the epilogue does not depend on the output
-// layout.  The chunk partials (fp64, fixed order) are added in chunk order by prune_sum_kernel.
+// its reference log-normaliser.  A workgroup takes entries and one chunk of kPruneChunk updated rows; the chunk
+// partials (fp64, fixed order) are added in chunk order by prune_sum_kernel.
 constexpr int kPruneChunk = 256;
-constexpr int kPruneEnt = 64;             // entries per workgroup (16 per wave)
-constexpr int kPruneRows = 32;            // rows staged per step
+constexpr int kPruneEnt = 64;             // entries per workgroup and block of a wave (16 per wave)
+constexpr int kPruneRows = 32;            // rows staged per step of the fp64 products
+
+struct PruneArgs {
+  const uint16_t *q, *k;
+  const int32_t* rows;
+  int n_rows;
+  const int32_t* cols;
+  int c_list, ns;
+  const float* lse_ref;
+  int N, H;
+  double sigma;
+  int n_chunks;
+  double* part;                           // [B, H, n_chunks, c_list - ns]
+  bool digits;                            // q and k are 16-byte aligned
+};
 
 template <int D>
-__global__ __launch_bounds__(256) void prune_mass_kernel(const uint16_t* __restrict__ q,
-                                                         const uint16_t* __restrict__ kc,
-                                                         const int32_t* __restrict__ rows, int k,
-                                                         const int32_t* __restrict__ cols, int c_list, int ns,
-                                                         const float* __restrict__ lse_ref, int N, int H,
-                                                         double sigma, int n_chunks, double* __restrict__ part) {
-  constexpr int QS = D + 1;               // padded row stride (doubles): the 16 rows of a read spread over banks
+struct PruneWide {
+  double qt[kPruneRows * (D + 1)];        // padded row stride: the 16 rows of a read spread over banks
+  double lse[kPruneRows];
+  int row[kPruneRows];
+};
+
+// 64 entries of a chunk by fp64 MFMAs (v_mfma_f64_16x16x4): a wave owns 16 entries (their K rows as the B
+// operand, in registers: lane l holds dim 4s + l / 16 of entry l % 16 for step s), the chunk's rows from `first` on are
+// staged 32 at a time in LDS as fp64 (the A operand: row l % 16, dim 4s + l / 16).  Which accumulator element is which
+// (row, entry) is read off two index products at the start, so the epilogue does not depend on the output layout.
+template <int D>
+__device__ __forceinline__ void prune_wide(const PruneArgs& a, int b, int h, int e_first, const int* s_rows, int p0,
+                                           int first, int p_end, double* __restrict__ part, PruneWide<D>& w,
+                                           double (*red)[16][17]) {
+  constexpr int QS = D + 1;
   constexpr int KSTEPS = D / 4;
-  __shared__ double qt[kPruneRows * QS];
-  __shared__ double q_lse[kPruneRows];
-  __shared__ int q_row[kPruneRows];
-  __shared__ double red[4][16][17];       // per wave: accumulators by (entry, row) for the ordered sum
-  __shared__ int s_rows[kPruneChunk];     // the chunk's updated rows
-  __shared__ int s_cnt[4];
-  const int h = blockIdx.y % H, chunk = blockIdx.y / H, b = blockIdx.z;
-  const int n_ent = c_list - ns;
+  const int n_ent = a.c_list - a.ns;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int l16 = lane & 15, kq = lane >> 4;
-  const int64_t stride = (int64_t)H * D;
-  const int32_t* cl = cols + ((int64_t)b * H + h) * c_list + ns;
-  const int32_t* rp = rows + (int64_t)b * k;
-  const int p_end = min(k, (chunk + 1) * kPruneChunk);
-  const int e_wave = blockIdx.x * kPruneEnt + wave * 16;     // first entry of this wave
+  const int64_t stride = (int64_t)a.H * D;
+  const int32_t* cl = a.cols + ((int64_t)b * a.H + h) * a.c_list + a.ns;
+  const int e_wave = e_first + wave * 16;                    // first entry of this wave
   const bool wave_ok = e_wave < n_ent;
   const int j_first = wave_ok ? cl[e_wave] : INT_MAX;        // entries ascend
-
-  // B operand: dims 4s + kq of entry e_wave + l16 (zero past the list's end)
-  double kb[KSTEPS];
+  double kb[KSTEPS];                       // dims 4s + kq of entry e_wave + l16 (zero past the list's end)
   {
     const int e = e_wave + l16;
     const bool ok = e < n_ent;
-    const uint16_t* src = kc + ((int64_t)b * N + (ok ? cl[e] : 0)) * stride + (int64_t)h * D + kq;
+    const uint16_t* src = a.k + ((int64_t)b * a.N + (ok ? cl[e] : 0)) * stride + (int64_t)h * D + kq;
 #pragma unroll
     for (int s = 0; s < KSTEPS; ++s) kb[s] = ok ? (double)bf16_to_f32(src[4 * s]) : 0.0;
   }
-  // which (row, entry) each accumulator element holds: D = A B with A = row index in k-column 0, B = 1 in
-  // k-row 0 gives the row; the transposed pair gives the entry
   int el_row[4], el_ent[4];
   mfma_f64_layout(l16, kq, el_row, el_ent);
   int el_j[4];                             // column id of each element's entry (INT_MAX past the end)
@@ -454,48 +433,35 @@ __global__ __launch_bounds__(256) void prune_mass_kernel(const uint16_t* __restr
     const int e = e_wave + el_ent[t];
     el_j[t] = e < n_ent ? cl[e] : INT_MAX;
   }
-  // the chunk's rows into LDS, and the first one that can see the workgroup's first entry (rows and
-  // entries ascend: the rows before it are counted with one ballot per wave)
-  const int p0 = chunk * kPruneChunk;
-  static_assert(kPruneChunk == 256, "one row of the chunk per thread");
-  {
-    const int j0 = cl[blockIdx.x * kPruneEnt];
-    const int p = p0 + (int)threadIdx.x;
-    const int i = p < p_end ? rp[p] : INT_MAX;
-    s_rows[threadIdx.x] = i;
-    const uint64_t before = __builtin_amdgcn_ballot_w64(i < j0);
-    if (lane == 0) s_cnt[wave] = __builtin_popcountll(before);
-  }
-  __syncthreads();
-  const int first = p0 + s_cnt[0] + s_cnt[1] + s_cnt[2] + s_cnt[3];
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
+  __syncthreads();
   for (int t0 = first; t0 < p_end; t0 += kPruneRows) {
     for (int x = threadIdx.x; x < kPruneRows * D; x += 256) {
       const int r = x / D, dd = x % D;
       const int p = t0 + r;
-      qt[r * QS + dd] = p < p_end ? (double)bf16_to_f32(q[((int64_t)b * N + s_rows[p - p0]) * stride + (int64_t)h * D + dd]) : 0.0;
+      w.qt[r * QS + dd] = p < p_end ? (double)bf16_to_f32(a.q[((int64_t)b * a.N + s_rows[p - p0]) * stride + (int64_t)h * D + dd]) : 0.0;
     }
     if (threadIdx.x < kPruneRows) {
       const int p = t0 + (int)threadIdx.x;
       const int i = p < p_end ? s_rows[p - p0] : -1;
-      q_row[threadIdx.x] = i;
-      q_lse[threadIdx.x] = p < p_end ? (double)lse_ref[((int64_t)b * N + i) * H + h] : 0.0;
+      w.row[threadIdx.x] = i;
+      w.lse[threadIdx.x] = p < p_end ? (double)a.lse_ref[((int64_t)b * a.N + i) * a.H + h] : 0.0;
     }
     __syncthreads();
 #pragma unroll
     for (int half = 0; half < kPruneRows / 16; ++half) {
       // uniform: skip 16 rows that all come before this wave's first entry
-      const int last_row = q_row[min(16 * half + 15, p_end - t0 - 1)];
+      const int last_row = w.row[min(16 * half + 15, p_end - t0 - 1)];
       if (wave_ok && last_row >= j_first) {
         f64x4 d4 = {0.0, 0.0, 0.0, 0.0};
-        const double* qa = qt + (16 * half + l16) * QS + kq;
+        const double* qa = w.qt + (16 * half + l16) * QS + kq;
 #pragma unroll
         for (int s = 0; s < KSTEPS; ++s) d4 = __builtin_amdgcn_mfma_f64_16x16x4f64(qa[4 * s], kb[s], d4, 0, 0, 0);
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
           const int r = 16 * half + el_row[t];
-          const int i = q_row[r];                                // -1 past the chunk's last row
-          if (i >= el_j[t]) acc[t] += exp(sigma * d4[t] - q_lse[r]);
+          const int i = w.row[r];                                // -1 past the chunk's last row
+          if (i >= el_j[t]) acc[t] += exp(a.sigma * d4[t] - w.lse[r]);
         }
       }
     }
@@ -509,7 +475,157 @@ __global__ __launch_bounds__(256) void prune_mass_kernel(const uint16_t* __restr
     double s = 0.0;
 #pragma unroll
     for (int r = 0; r < 16; ++r) s += red[wave][lane][r];
-    part[(((int64_t)b * H + h) * n_chunks + chunk) * n_ent + e_wave + lane] = s;
+    part[e_wave + lane] = s;
+  }
+  __syncthreads();
+}
+
+// A wave owns NB blocks of 16 entries as digits in registers, a workgroup 64 NB entries; the chunk's rows are turned
+// into digits 64 at a time (16 per wave) into LDS, the rows of the next 64 on their way while these are multiplied.
+// Where the digits do not serve the rows and entries of the workgroup, or a log-normaliser is out of their range, the
+// workgroup takes fp64 products.  At 1638 rows and 1532 entries of 16 heads x 128: 366 us in fp64 products (their matrix
+// rate), 105 us so.
+template <int D, int NB>
+__global__ __launch_bounds__(256, 2) void prune_mass_kernel(PruneArgs a) {
+  constexpr int KS = D / 64;
+  constexpr size_t kDig = sizeof(uint4) * kDigStage * 4 * KS * 64;
+  constexpr size_t kBuf = kDig > sizeof(PruneWide<D>) ? kDig : sizeof(PruneWide<D>);
+  static_assert(sizeof(double) * 4 * 16 * 17 <= kBuf, "the fp64 path's sums reuse the buffer");
+  __shared__ __attribute__((aligned(16))) char buf[kBuf];
+  __shared__ int s_rows[kPruneChunk];     // the chunk's updated rows
+  __shared__ int s_cnt[4];
+  __shared__ DigitStat s_own[4], s_st[kDigStage];
+  __shared__ double s_lse[kDigStage * 16];
+  __shared__ int s_id[kDigStage * 16];
+  const int h = blockIdx.y % a.H, chunk = blockIdx.y / a.H, b = blockIdx.z;
+  const int n_ent = a.c_list - a.ns;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l16 = lane & 15, g = lane >> 4;
+  const int64_t stride = (int64_t)a.H * D;
+  const int32_t* cl = a.cols + ((int64_t)b * a.H + h) * a.c_list + a.ns;
+  const int32_t* rp = a.rows + (int64_t)b * a.n_rows;
+  const int p0 = chunk * kPruneChunk, p_end = min(a.n_rows, p0 + kPruneChunk);
+  const int e_wg = blockIdx.x * kPruneEnt * NB;              // entry e_wg + 64 nb + 16 wave + l16 is the lane's
+  double* part = a.part + (((int64_t)b * a.H + h) * a.n_chunks + chunk) * n_ent;
+  // the chunk's rows into LDS, and the first one that can see the workgroup's first entry (rows and
+  // entries ascend: the rows before it are counted with one ballot per wave)
+  static_assert(kPruneChunk == 256, "one row of the chunk per thread");
+  {
+    const int p = p0 + (int)threadIdx.x;
+    const int i = p < p_end ? rp[p] : INT_MAX;
+    s_rows[threadIdx.x] = i;
+    const uint64_t before = __builtin_amdgcn_ballot_w64(i < cl[e_wg]);
+    if (lane == 0) s_cnt[wave] = __builtin_popcountll(before);
+  }
+  DigitBlock<D> own[NB];
+  int j[NB], j_lo[NB], j_hi[NB];          // column of the lane's entry, and the first and last of the block
+  double f_own[NB], acc[NB];
+  DigitStat st_own = {0.0f, 0.0f, 0.0f, 0};
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    const int e0 = e_wg + 64 * nb + 16 * wave, e = e0 + l16;
+    j[nb] = e < n_ent ? cl[e] : INT_MAX;
+    j_lo[nb] = e0 < n_ent ? cl[e0] : INT_MAX;
+    j_hi[nb] = e0 + 15 < n_ent ? cl[e0 + 15] : INT_MAX;
+    uint4 w[2 * KS];
+#pragma unroll
+    for (int x = 0; x < 2 * KS; ++x) w[x] = make_uint4(0, 0, 0, 0);
+    if (a.digits && e < n_ent) {
+      const uint16_t* src = a.k + ((int64_t)b * a.N + j[nb]) * stride + (int64_t)h * D + 16 * g;
+#pragma unroll
+      for (int x = 0; x < 2 * KS; ++x) w[x] = *reinterpret_cast<const uint4*>(src + 64 * (x >> 1) + 8 * (x & 1));
+    }
+    DigitStat st;
+    own[nb] = make_digits<D>(w, st);
+    f_own[nb] = __builtin_ldexp(a.sigma * 0x1.71547652b82fep+16, st.e - 30);
+    acc[nb] = 0.0;
+    st_own.res = fmaxf(st_own.res, st.res);
+    st_own.top = fmaxf(st_own.top, st.top);
+    st_own.norm = fmaxf(st_own.norm, st.norm);
+  }
+  if (lane == 0) s_own[wave] = st_own;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    st_own.res = fmaxf(st_own.res, s_own[w].res);
+    st_own.top = fmaxf(st_own.top, s_own[w].top);
+    st_own.norm = fmaxf(st_own.norm, s_own[w].norm);
+  }
+  const int first = p0 + s_cnt[0] + s_cnt[1] + s_cnt[2] + s_cnt[3];
+  bool serve = a.digits;
+  // the wave's rows of a stage: 16, row l16 of them the lane's
+  uint4 w[2 * KS];
+  int id = -1;
+  float lse = 0.0f;
+  auto fetch = [&](int t0) __attribute__((always_inline)) {
+    const int p = t0 + 16 * wave + l16;
+    id = p < p_end ? s_rows[p - p0] : -1;
+    lse = id >= 0 ? a.lse_ref[((int64_t)b * a.N + id) * a.H + h] : 0.0f;
+#pragma unroll
+    for (int x = 0; x < 2 * KS; ++x) w[x] = make_uint4(0, 0, 0, 0);
+    if (a.digits && id >= 0) {
+      const uint16_t* src = a.q + ((int64_t)b * a.N + id) * stride + (int64_t)h * D + 16 * g;
+#pragma unroll
+      for (int x = 0; x < 2 * KS; ++x) w[x] = *reinterpret_cast<const uint4*>(src + 64 * (x >> 1) + 8 * (x & 1));
+    }
+  };
+  uint4* dig = reinterpret_cast<uint4*>(buf);
+  fetch(first);
+  for (int t0 = first; serve && t0 < p_end; t0 += 16 * kDigStage) {
+    {
+      DigitStat st;
+      const DigitBlock<D> o = make_digits<D>(w, st);
+      if (__builtin_amdgcn_ballot_w64(!(fabsf(lse) <= 330.0f)) != 0) st.norm = INFINITY;   // (also NaN)
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+          reinterpret_cast<i32x4*>(dig)[((wave * 4 + s) * KS + ks) * 64 + lane] = o.d[s][ks];
+      if (lane == 0) s_st[wave] = st;
+      if (lane < 16) {
+        s_lse[16 * wave + lane] = (double)lse * 0x1.71547652b82fep+0;
+        s_id[16 * wave + lane] = id;
+      }
+    }
+    fetch(t0 + 16 * kDigStage);            // (past the last row: nothing is loaded)
+    __syncthreads();
+#pragma unroll
+    for (int x = 0; x < kDigStage; ++x) serve = serve && digits_serve(st_own, s_st[x], D, a.sigma);
+    const int row_lo = s_id[0], row_hi = s_rows[min(t0 + 16 * kDigStage, p_end) - 1 - p0];
+    if (serve && row_hi >= j_lo[0]) {      // uniform in the wave
+      auto add = [&](const DigitSums& o, int x, int nb, auto edge) __attribute__((always_inline)) {
+        const double f = __builtin_ldexp(f_own[nb], s_st[x].e - 30);
+        double e[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const int r = 16 * x + 4 * g + t;
+          double z = fma(digit_dot(o, t), f, -s_lse[r]);
+          if (edge.value) z = s_id[r] >= j[nb] ? z : -1000.0;
+          e[t] = exp2_f64(z);
+        }
+        acc[nb] += (e[0] + e[1]) + (e[2] + e[3]);
+      };
+      if (row_lo >= j_hi[NB - 1] && t0 + 16 * kDigStage <= p_end)
+        digit_stage<D, NB>(dig, own, [&](const DigitSums& o, int x, int nb) __attribute__((always_inline)) { add(o, x, nb, std::false_type{}); });
+      else
+        digit_stage<D, NB>(dig, own, [&](const DigitSums& o, int x, int nb) __attribute__((always_inline)) { add(o, x, nb, std::true_type{}); });
+    }
+    __syncthreads();
+  }
+  if (!serve) {                            // the same in every wave
+    for (int nb = 0; nb < NB; ++nb)
+      if (e_wg + 64 * nb < n_ent)
+        prune_wide<D>(a, b, h, e_wg + 64 * nb, s_rows, p0, first, p_end, part, *reinterpret_cast<PruneWide<D>*>(buf),
+                      reinterpret_cast<double (*)[16][17]>(buf));
+    return;
+  }
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    double s = acc[nb];
+    s += __shfl_xor(s, 16, 64);
+    s += __shfl_xor(s, 32, 64);
+    const int e = e_wg + 64 * nb + 16 * wave + lane;
+    if (lane < 16 && e < n_ent) part[e] = s;
   }
 }
 
@@ -619,8 +735,10 @@ extern "C" int fl_column_scores(const uint16_t* q, const uint16_t* k_cache, int 
       int rc = check_launch("cs_digits_kernel");
       if (rc != FL_OK) return rc;
     }
-    // two blocks per wave halve the reads of the staged digits; one where that leaves less than two workgroups per CU
-    const bool wide = (int64_t)((a.nblk + 7) / 8) * a.n_seg >= 512;
+    // two blocks per wave halve the reads of the staged digits; with one, three workgroups share a CU and end more
+    // evenly: the statistic of 16 heads x 128 at N = 8192 (1024 workgroups of two) 1.46 ms against 1.51, at N = 4096 (512)
+    // 0.55 ms against 0.50
+    const bool wide = (int64_t)((a.nblk + 7) / 8) * a.n_seg >= 1024;
     int rc;
     if (d == 128) rc = wide ? launch_colscore<128, 2>(a, st) : launch_colscore<128, 1>(a, st);
     else rc = wide ? launch_colscore<64, 2>(a, st) : launch_colscore<64, 1>(a, st);
@@ -674,13 +792,20 @@ extern "C" int fl_prune_columns(const uint16_t* q, const uint16_t* k_cache, cons
   FL_REQUIRE((int64_t)H * n_chunks <= 65535, FL_E_SHAPE, "fl_prune_columns: H * ceil(k / %d) above 65535",
              kPruneChunk);
   double* part = static_cast<double*>(ws);
-  dim3 grid((n_ent + kPruneEnt - 1) / kPruneEnt, H * n_chunks, B);
-  if (d == 128)
-    prune_mass_kernel<128><<<grid, 256, 0, st>>>(q, k_cache, rows, k, cols, c_list, ns, lse_ref, N, H, sm_scale,
-                                                 n_chunks, part);
-  else
-    prune_mass_kernel<64><<<grid, 256, 0, st>>>(q, k_cache, rows, k, cols, c_list, ns, lse_ref, N, H, sm_scale,
-                                                n_chunks, part);
+  const bool digits = ((reinterpret_cast<uintptr_t>(q) | reinterpret_cast<uintptr_t>(k_cache)) & 15) == 0;
+  const PruneArgs a{q, k_cache, rows, k, cols, c_list, ns, lse_ref, N, H, sm_scale, n_chunks, part, digits};
+  // two blocks of entries per wave halve the conversions of the rows; one where that leaves less than two workgroups
+  // per CU
+  const int64_t wide = (int64_t)((n_ent + 2 * kPruneEnt - 1) / (2 * kPruneEnt)) * H * n_chunks * B;
+  const int nb = wide >= 512 ? 2 : 1;
+  const dim3 grid((n_ent + nb * kPruneEnt - 1) / (nb * kPruneEnt), H * n_chunks, B);
+  if (d == 128) {
+    if (nb == 2) prune_mass_kernel<128, 2><<<grid, 256, 0, st>>>(a);
+    else prune_mass_kernel<128, 1><<<grid, 256, 0, st>>>(a);
+  } else {
+    if (nb == 2) prune_mass_kernel<64, 2><<<grid, 256, 0, st>>>(a);
+    else prune_mass_kernel<64, 1><<<grid, 256, 0, st>>>(a);
+  }
   int rc = check_launch("prune_mass_kernel");
   if (rc != FL_OK) return rc;
   const int64_t total = (int64_t)B * H * n_ent;

@@ -10,7 +10,7 @@
 // Thirteen 8-bit products at twice the bf16 rate replace the fp64 product at 1/32 of it (2.5 PFLOP/s against
 // 78.6 TFLOP/s): about 5 times the rate of the fp64 matrix instructions for the same sums.
 #pragma once
-#include "fl_common.h"
+#include "fl_attn_util.h"
 
 namespace fl {
 
@@ -68,6 +68,17 @@ struct DigitBlock {
   i32x4 d[4][D / 64];
 };
 
+// max over the 16 lanes of a row (rotations within the row, no LDS)
+__device__ __forceinline__ float row16_max(float x) {
+#define FL_ROR(n) __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x120 + (n), 0xf, 0xf, false))
+  x = fmaxf(x, FL_ROR(8));
+  x = fmaxf(x, FL_ROR(4));
+  x = fmaxf(x, FL_ROR(2));
+  x = fmaxf(x, FL_ROR(1));
+#undef FL_ROR
+  return x;
+}
+
 // w: the lane's 2 KS loads of 8 elements.  stat: of the 16 vectors, the same in every lane.
 template <int D>
 __device__ __forceinline__ DigitBlock<D> make_digits(const uint4 (&w)[2 * (D / 64)], DigitStat& stat) {
@@ -76,8 +87,7 @@ __device__ __forceinline__ DigitBlock<D> make_digits(const uint4 (&w)[2 * (D / 6
   uint32_t m = 0;
 #pragma unroll
   for (int x = 0; x < 2 * KS; ++x) m = max_abs_bits(w[x], m);
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off, 64));
+  m = (uint32_t)row4_max(row16_max((float)m));              // (15 bits: exact as floats)
   const int e = digit_exponent(m);
   const bool finite = m < 0x7F80u;
   const float scale = digit_scale(e);
@@ -102,16 +112,8 @@ __device__ __forceinline__ DigitBlock<D> make_digits(const uint4 (&w)[2 * (D / 6
     }
   }
   const float unit = __uint_as_float((uint32_t)max(e - 30 + 127, 1) << 23);     // 2^(e - 30), at least 2^-126
-  res += __shfl_xor(res, 16, 64);
-  res += __shfl_xor(res, 32, 64);
-  n2 += __shfl_xor(n2, 16, 64);
-  n2 += __shfl_xor(n2, 32, 64);
-  float norm = sqrtf(n2);
-#pragma unroll
-  for (int off = 1; off < 16; off <<= 1) {
-    res = fmaxf(res, __shfl_xor(res, off, 64));
-    norm = fmaxf(norm, __shfl_xor(norm, off, 64));
-  }
+  res = row16_max(row4_add(res));
+  const float norm = sqrtf(row16_max(row4_add(n2)));
   stat.res = finite ? res * unit : INFINITY;
   stat.top = finite ? unit * 0x1p30f : INFINITY;
   stat.norm = finite ? norm : INFINITY;
@@ -166,6 +168,38 @@ __device__ __forceinline__ void digit_sums(const i32x4 (&a)[4][D / 64], const Di
 __device__ __forceinline__ double digit_dot(const DigitSums& o, int t) {
   const double p = fma((double)(o.s[4][t] * 256 + o.s[3][t]), 65536.0, (double)(o.s[2][t] * 256 + o.s[1][t]));
   return fma(p, 256.0, (double)o.s[0][t]);
+}
+
+constexpr int kDigStage = 4;              // 16-vector blocks staged in LDS per step
+
+// The kDigStage staged blocks (dig: as 16-byte pieces by block, digit 3 .. 0, 64 dims and lane) against a wave's NB own
+// ones: add(sums, staged block, own block) for each pair.  The products of a pair are issued between the vector
+// instructions of the add before: a product's matrix cycles cover four of them.
+template <int D, int NB, int STG = kDigStage, typename Add>
+__device__ __forceinline__ void digit_stage(const uint4* dig, const DigitBlock<D> (&own)[NB], Add add) {
+  constexpr int KS = D / 64;
+  const i32x4* src = reinterpret_cast<const i32x4*>(dig) + (threadIdx.x & 63);
+  i32x4 d[4][KS];
+  DigitSums o[2];
+#pragma unroll
+  for (int i = -1; i < STG * NB; ++i) {
+    if (i + 1 < STG * NB) {
+      if ((i + 1) % NB == 0) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+          for (int ks = 0; ks < KS; ++ks) d[s][ks] = src[((i + 1) / NB * 4 * KS + s * KS + ks) * 64];
+      }
+      digit_sums<D>(d, own[(i + 1) % NB], o[(i + 1) & 1]);
+    }
+    if (i < 0) continue;
+    add(o[i & 1], i / NB, i % NB);
+#pragma unroll
+    for (int y = 0; y < 13 * KS; ++y) {
+      __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x2, KS == 2 ? 4 : 7, 0);
+    }
+  }
 }
 
 // 2^x for |x| <= 1000: 2^rint(x) times a degree-10 polynomial of the rest (the Chebyshev interpolant of 2^r on

@@ -1,4 +1,4 @@
-"""GPU parity of the fp64 column statistic on integer digits (fl_digits.h) where its tiles and ranges end.
+"""GPU parity of the fp64 column and list statistics on integer digits (fl_digits.h) where its tiles and ranges end.
 
 Keys within one fp32 ulp of the oracle's fp64 statistic rounded to fp32: the digits hold the dot products to better
 than 2^-24 of an exponent, or the (batch, head) takes the fp64 products.  Lengths: around the 16-vector blocks, the
@@ -14,6 +14,7 @@ import torch
 
 from gpu_util import assert_keys_close, down, say, up_bf16
 from oracle import attention as att
+from oracle import prune
 from oracle.numerics import bf16_to_f64, f32_to_bf16
 
 pytestmark = pytest.mark.gpu
@@ -66,8 +67,8 @@ def test_lengths(F, B, N, H, d):
 
 @pytest.mark.parametrize("d", [64, 128])
 def test_two_blocks_per_wave(F, d):
-    """128-vector workgroups (at least 512 of them), the last one partial."""
-    B, N, H = 2, 2047, 16
+    """128-vector workgroups (at least 1024 of them), the last one partial."""
+    B, N, H = 4, 2047, 16
     q, k = _inputs("normal", B, N, H, d)
     got = down(F.column_scores(up_bf16(q), up_bf16(k)))
     _check(F, "normal", B, N, H, d, got, q, k, (0, 9))
@@ -118,3 +119,53 @@ def test_small_workspace(F):
     for b in range(2):
         for h in range(3):
             assert_keys_close(got[b, h], want[b, h], f"b={b} h={h}")
+
+
+# ---- the list statistic -----------------------------------------------------------------------------------
+def _check_prune(F, what, q, k, rows, cols, lse, ns, heads):
+    B, N, H, d = q.shape
+    _, got = F.prune_columns(up_bf16(q), up_bf16(k), torch.from_numpy(rows).cuda(), torch.from_numpy(cols).cuda(),
+                             torch.from_numpy(lse).cuda(), ns, 5)
+    got = down(got)
+    for b in range(B):
+        for h in heads:
+            stat = prune.column_mass(cols[b, h], rows[b], bf16_to_f64(q[b, :, h]), bf16_to_f64(k[b, :, h]),
+                                     lse[b, :, h].astype(np.float64), 1 / np.sqrt(d), ns)
+            assert_keys_close(got[b, h], stat.astype(np.float32), f"{what} b={b} h={h}")
+
+
+def _prune_state(kind, B, N, H, d, n_ent, k):
+    rng = np.random.default_rng(N + d)
+    q, kc = _inputs(kind, B, N, H, d)
+    pick = lambda n: np.sort(rng.choice(N - 4, n, replace=False)).astype(np.int32) + 4  # noqa: E731
+    rows = np.stack([pick(k) for _ in range(B)])
+    cols = np.stack([np.stack([np.concatenate([np.arange(4, dtype=np.int32), pick(n_ent)]) for _ in range(H)])
+                     for _ in range(B)])
+    lse = rng.normal(5.0, 1.0, (B, N, H)).astype(np.float32)
+    return q, kc, rows, cols, lse
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_prune_two_blocks_per_wave(F, d):
+    """128-entry workgroups (528 of them) with a partial last one, the last chunk of rows partial."""
+    q, k, rows, cols, lse = _prune_state("normal", 2, 2400, 8, d, 1301, 700)
+    _check_prune(F, "normal", q, k, rows, cols, lse, 4, (0, 5))
+
+
+@pytest.mark.parametrize("kind", ["tiny-both", "zeros", "large", "outlier", "wide"])
+def test_prune_values(F, kind):
+    q, k, rows, cols, lse = _prune_state(kind, 1, 400, 2, 128, 70, 300)
+    if kind == "large":
+        lse += 640     # (the logits reach about 600: the keys stay finite)
+    _check_prune(F, kind, q, k, rows, cols, lse, 4, range(2))
+
+
+def test_prune_normaliser_out_of_range(F):
+    """A log-normaliser beyond the digits' exponents sends its chunk of rows to the fp64 products."""
+    q, k, rows, cols, lse = _prune_state("normal", 1, 400, 2, 64, 70, 300)
+    lse[0, rows[0, 290]] = 400.0
+    lse[0, rows[0, 10], 1] = -340.0
+    _, got = F.prune_columns(up_bf16(q), up_bf16(k), torch.from_numpy(rows).cuda(), torch.from_numpy(cols).cuda(),
+                             torch.from_numpy(lse).cuda(), 4, 5)
+    assert np.isinf(down(got)[0, 1, 0])       # exp(340) is beyond fp32
+    _check_prune(F, "normaliser", q, k, rows, cols, lse, 4, (0,))
