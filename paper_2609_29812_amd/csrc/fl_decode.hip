@@ -8,15 +8,15 @@
 // column) and forms its mass m' = sum_{S'} p_j and subtract term sub' = sum_{S'} p_j V_j.  Within a row
 // p_j grows with l_j, so the ranking key is fp32(l_j), available before L is known.
 //
-// One row per (b, h) is a GEMV: HBM-bound, split over columns.  Two launches:
+// One row per (b, h) is a GEMV: HBM-bound, split over columns.  Two launches, or three:
 //   decode_partial   chunks of 128 positions: fp64 logits (exact bf16 products, fp64 sums) and their fp32
 //                    ranking keys (forced columns +inf), the chunk's max and exp-sum, and the
 //                    exp-weighted sum of its V rows (fp32); K and V rows are each read once, 16 bytes per
 //                    lane, D/8 lanes per row.
-//   decode_finalize  one 1024-thread workgroup per (b, h): merges the chunks into L and the output, and
-//                    forms the next loop's columns, mass and subtract term: directly when every column
-//                    is kept, else by the radix top-k of fl_topk.h over the keys and a gather of the
-//                    selected V rows (read once more).
+//   decode_finalize  per (b, h), one workgroup merges the chunks into L and the output, and others form the next
+//                    loop's columns, mass and subtract term by the radix top-k of fl_topk.h over the keys and a
+//                    gather of the selected V rows (read once more); nothing to select when every column is kept.
+//   decode_sum       adds the sums of several selecting workgroups.
 #include "fl_common.h"
 #include "fl_topk.h"
 
@@ -48,7 +48,9 @@ struct DecodeArgs {
   double* psum;              // ws [B*H, nch] chunk exp-sum
   float* pacc;               // ws [B*H, nch, D]
   float* key;                // ws [B*H, n]
-  const int32_t* sel;        // ws [B*H, c_next] selected positions
+  const int32_t* sel;        // ws [B*H, c_next] selected positions (one selecting workgroup per (b, h)), or
+  double* part_mass;         //    [B*H, n_sel] and
+  float* part_sub;           //    [B*H, n_sel, D] sums of the shares (more than one)
   int32_t* cols_next;        // [B, H, c_next]
   float* mass_next;          // [B, H]
   float* sub_next;           // [B, H, D]
@@ -187,106 +189,125 @@ __global__ __launch_bounds__(256) void decode_partial_kernel(DecodeArgs a) {
   }
 }
 
-// ---- finalize: one 1024-thread workgroup per (b, h) ----------------------------------------------------
-// (1) merges the chunks into L and the output; (2) with c_next > 0, the next loop's columns, mass m' =
-// sum_{S'} p_j and subtract term sub' = sum_{S'} p_j V_j.  When the next loop keeps every column
-// (c_next = n) these are the columns themselves, m' = m (the probabilities over S sum to m) and sub' = the
-// add term just formed.  Otherwise the radix top-k of fl_topk.h writes the selected positions (ascending)
-// to the workspace, and windows of kSelWin of them are gathered: ids, logits and weights into LDS, then
-// their V rows (every load of a window issued before any use); the waves' sums are added in order
-// (deterministic).
-template <int D, int M>
+// ---- finalize ------------------------------------------------------------------------------------------
+// Workgroup y = 0 of each (b, h) merges the chunks into L and the output; when the next loop keeps every column
+// (c_next = n) it also writes the columns themselves, m' = m (the probabilities over S sum to m) and sub' = the
+// add term just formed.  Otherwise the workgroups y = 1 .. n_sel select the next loop's columns and sum their
+// probabilities and values: each runs the radix top-k of fl_topk.h over all keys, writes its share of the selected
+// positions (ascending) and gathers their logits and V rows (ids and weights in LDS, every V load issued before any
+// use).  With one of them the positions go through the workspace in windows of kSelWin; with more, each has one
+// window in LDS, and decode_sum_kernel adds their sums in order (deterministic).
+//
+// Bound by latency: a top-k over 32K keys takes about 20 us on one workgroup however few of them run, and the
+// gather of 2048 rows by one workgroup as long again.  At 16 heads over 32K columns, c_next = 2048, one workgroup for
+// all of it took 49 us, 32 us so (28 and 4 for the sum; the merge beside the selection, eight gathers side by side).
+
+// L = M + log S over the chunks' maxima and exp-sums, in every wave
+__device__ __forceinline__ void merge_normaliser(const DecodeArgs& a, int bh, double& Mx, double& S) {
+  const int lane = threadIdx.x & 63;
+  const double* pm = a.pmax + (int64_t)bh * a.nch;
+  const double* ps = a.psum + (int64_t)bh * a.nch;
+  double mx = -INFINITY;
+  for (int c = lane; c < a.nch; c += 64) mx = fmax(mx, pm[c]);
+  Mx = wave_max_f64(mx);
+  double es = 0.0;
+  for (int c = lane; c < a.nch; c += 64) es += ps[c] * exp(pm[c] - Mx);
+  S = wave_sum_f64_dec(es);
+}
+
+template <int D>
+__device__ __forceinline__ void decode_merge(const DecodeArgs& a, int bh, double m, float* s_f, float (*s_acc)[D]) {
+  constexpr int PARTS = kTopkThreads / D;    // threads per output dimension
+  const int tid = threadIdx.x;
+  const bool dense = a.cols == nullptr;
+  double Mx, S;
+  merge_normaliser(a, bh, Mx, S);
+  for (int c = tid; c < a.nch; c += kTopkThreads) s_f[c] = (float)(m * exp(a.pmax[(int64_t)bh * a.nch + c] - Mx) / S);
+  __syncthreads();
+  {
+    // thread (part, dd) adds the chunks part, part + PARTS, ...; the parts are then added in order
+    const int dd = tid % D, part = tid / D;
+    const float* pa = a.pacc + (int64_t)bh * a.nch * D + dd;
+    float add = 0.0f;
+#pragma unroll 8
+    for (int c = part; c < a.nch; c += PARTS) add = fmaf(s_f[c], pa[(int64_t)c * D], add);
+    s_acc[part][dd] = add;
+  }
+  __syncthreads();
+  const bool keep_all = a.c_next == a.n;
+  if (tid < D) {
+    float o_add = 0.0f;
+#pragma unroll
+    for (int q = 0; q < PARTS; ++q) o_add += s_acc[q][tid];
+    const int64_t od = (int64_t)bh * D + tid;
+    a.o[od] = dense ? o_add : a.o[od] - a.sub[od] + o_add;
+    if (keep_all) a.sub_next[od] = o_add;
+  }
+  if (tid == 0 && a.lse) a.lse[bh] = (float)(Mx + log(S));
+  if (keep_all) {
+    for (int i = tid; i < a.n; i += kTopkThreads) a.cols_next[(int64_t)bh * a.n + i] = dec_col(a, bh, i);
+    if (tid == 0) a.mass_next[bh] = (float)m;
+  }
+}
+
+template <int D, int M, int NH>
 __global__ __launch_bounds__(kTopkThreads) void decode_finalize_kernel(DecodeArgs a) {
   constexpr int NW = kTopkThreads / 64;      // waves
-  constexpr int PARTS = kTopkThreads / D;    // threads per output dimension in the merge
   constexpr int LPC = D / 8;                 // lanes per V row (16 bytes each)
   constexpr int CPW = 64 / LPC;              // rows per wave instruction
   constexpr int IT = kSelWin / (NW * CPW);   // window rows per lane
   static_assert(IT * NW * CPW == kSelWin && kSelWin == kTopkThreads, "one id per thread, IT rows per lane");
   constexpr int BUF = NW * D > 2 * kSelWin ? NW * D : 2 * kSelWin;
+  typedef TopkShared<M, kTopkThreads, NH> Topk;
+  __shared__ __attribute__((aligned(16))) Topk topk;
+  static_assert(sizeof(topk.hist) >= BUF * sizeof(float), "the sums and a window's ids and weights take its place");
   __shared__ double s_m[NW];
-  __shared__ double s_l;
   __shared__ float s_f[512];                 // chunk weights (nch <= 512)
-  __shared__ __attribute__((aligned(16))) float s_buf[BUF];   // partial sums; a window's ids and weights
+  __shared__ int32_t s_sel[kSelWin];         // a window's selected positions
+  float* s_buf = reinterpret_cast<float*>(topk.hist);
   float (*s_acc)[D] = reinterpret_cast<float (*)[D]>(s_buf);
   int32_t* s_col = reinterpret_cast<int32_t*>(s_buf);
   float* s_w = s_buf + kSelWin;
   const int bh = blockIdx.x;
   const int b = bh / a.H, h = bh % a.H;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const bool dense = a.cols == nullptr;
-  const double m = dense ? 1.0 : (double)a.mass[bh];
-  // (1) L = M + log S over the chunks' maxima and exp-sums; the add term and the output
-  double mx = -INFINITY;
-  for (int c = tid; c < a.nch; c += kTopkThreads) mx = fmax(mx, a.pmax[(int64_t)bh * a.nch + c]);
-  mx = wave_max_f64(mx);
-  if (lane == 0) s_m[wave] = mx;
-  __syncthreads();
-  double Mx = s_m[0];
-#pragma unroll
-  for (int w = 1; w < NW; ++w) Mx = fmax(Mx, s_m[w]);
-  __syncthreads();
-  double es = 0.0;
-  for (int c = tid; c < a.nch; c += kTopkThreads) {
-    const int64_t sidx = (int64_t)bh * a.nch + c;
-    es += a.psum[sidx] * exp(a.pmax[sidx] - Mx);
-  }
-  es = wave_sum_f64_dec(es);
-  if (lane == 0) s_m[wave] = es;
-  __syncthreads();
-  if (tid == 0) {
-    double S = 0.0;
-    for (int w = 0; w < NW; ++w) S += s_m[w];
-    s_l = S;
-  }
-  __syncthreads();
-  const double S = s_l;
-  const double L = Mx + log(S);
-  for (int c = tid; c < a.nch; c += kTopkThreads) s_f[c] = (float)(m * exp(a.pmax[(int64_t)bh * a.nch + c] - Mx) / S);
-  __syncthreads();
-  {
-    // thread (part, dd) adds the chunks part, part + PARTS, ...; the parts are then added in order
-    const int dd = tid % D, part = tid / D;
-    float add = 0.0f;
-    for (int c = part; c < a.nch; c += PARTS) add = fmaf(s_f[c], a.pacc[((int64_t)bh * a.nch + c) * D + dd], add);
-    s_acc[part][dd] = add;
-  }
-  __syncthreads();
-  float o_add = 0.0f;
-  if (tid < D) {
-#pragma unroll
-    for (int q = 0; q < PARTS; ++q) o_add += s_acc[q][tid];
-    const int64_t od = (int64_t)bh * D + tid;
-    a.o[od] = dense ? o_add : a.o[od] - a.sub[od] + o_add;
-  }
-  if (tid == 0 && a.lse) a.lse[bh] = (float)L;
-  if (a.c_next == 0) return;               // uniform
-  if (a.c_next == a.n) {                   // every column kept
-    for (int i = tid; i < a.n; i += kTopkThreads) a.cols_next[(int64_t)bh * a.n + i] = dec_col(a, bh, i);
-    if (tid < D) a.sub_next[(int64_t)bh * D + tid] = o_add;
-    if (tid == 0) a.mass_next[bh] = (float)m;
+  const double m = a.cols ? (double)a.mass[bh] : 1.0;
+  if (blockIdx.y == 0) {                     // uniform
+    decode_merge<D>(a, bh, m, s_f, s_acc);
     return;
   }
-  // (2) the selected positions, ascending, into the workspace; this workgroup's writes are visible to
-  // its own threads after a workgroup-scope release and acquire around the barrier
+  // this workgroup's share [lo0, hi0) of the selected positions
+  const int n_sel = gridDim.y - 1, y = blockIdx.y - 1;
+  const int share = (a.c_next + n_sel - 1) / n_sel;
+  const int lo0 = y * share, hi0 = min(a.c_next, lo0 + share);
   int32_t* sel = const_cast<int32_t*>(a.sel) + (int64_t)bh * a.c_next;
-  topk_block<M>(a.key + (int64_t)bh * a.n, a.n, a.c_next, nullptr, 0, sel, 0, nullptr, 0);
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  const float* keys = a.key + (int64_t)bh * a.n;
+  if (n_sel == 1) {
+    // the workgroup's writes are visible to its own threads after a workgroup-scope release and acquire around the
+    // barrier
+    topk_block<M, kTopkThreads, NH>(topk, keys, a.n, a.c_next, nullptr, 0, sel, 0, nullptr, 0);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  } else {
+    topk_block<M, kTopkThreads, NH>(topk, keys, a.n, a.c_next, nullptr, 0, s_sel, 0, nullptr, 0, lo0, hi0);
+  }
+  double Mx, S;
+  merge_normaliser(a, bh, Mx, S);
+  const double L = Mx + log(S);
   __syncthreads();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
   const int sl = lane % LPC, grp = lane / LPC;
   const int64_t HD = (int64_t)a.H * D;
   double ms = 0.0;
   float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  for (int lo = 0; lo < a.c_next; lo += kSelWin) {
+  for (int lo = lo0; lo < hi0; lo += kSelWin) {
+    const int rows = min(kSelWin, hi0 - lo);
     // ids, weights p_j = m exp(l_j - L) and the next loop's columns of the window (thread t: entry t)
     {
-      const int i = lo + tid;
-      const bool ok = i < a.c_next;
-      const int p = ok ? sel[i] : 0;
+      const bool ok = tid < rows;
+      const int p = ok ? (n_sel == 1 ? sel[lo + tid] : s_sel[tid]) : 0;
       const int col = dec_col(a, bh, p);
       const double pr = ok ? m * exp(a.logit[(int64_t)bh * a.n + p] - L) : 0.0;
-      if (ok) a.cols_next[(int64_t)bh * a.c_next + i] = col;
+      if (ok) a.cols_next[(int64_t)bh * a.c_next + lo + tid] = col;
       ms += pr;
       s_col[tid] = col;
       s_w[tid] = (float)pr;
@@ -297,12 +318,15 @@ __global__ __launch_bounds__(kTopkThreads) void decode_finalize_kernel(DecodeArg
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
       const int e = wave * CPW + grp + it * NW * CPW;
-      vw[it] = *reinterpret_cast<const uint4*>(a.v + ((int64_t)b * a.T + s_col[e]) * HD + (int64_t)h * D + 8 * sl);
+      vw[it] = make_uint4(0, 0, 0, 0);
+      if (it * NW * CPW < rows)              // uniform
+        vw[it] = *reinterpret_cast<const uint4*>(a.v + ((int64_t)b * a.T + s_col[e]) * HD + (int64_t)h * D + 8 * sl);
     }
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
+      if (it * NW * CPW >= rows) continue;   // uniform
       const int e = wave * CPW + grp + it * NW * CPW;
-      const float wf = s_w[e];             // 0 past the end of the selection
+      const float wf = s_w[e];               // 0 past the end of the share
       const uint32_t ws[4] = {vw[it].x, vw[it].y, vw[it].z, vw[it].w};
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
@@ -310,7 +334,7 @@ __global__ __launch_bounds__(kTopkThreads) void decode_finalize_kernel(DecodeArg
         acc[2 * t + 1] = fmaf(wf, bf16_to_f32(ws[t] >> 16), acc[2 * t + 1]);
       }
     }
-    __syncthreads();                       // the window's ids and weights are no longer read
+    __syncthreads();                         // the window's ids and weights are no longer read
   }
   ms = wave_sum_f64_dec(ms);
 #pragma unroll
@@ -322,17 +346,43 @@ __global__ __launch_bounds__(kTopkThreads) void decode_finalize_kernel(DecodeArg
   }
   if (lane == 0) s_m[wave] = ms;
   __syncthreads();
+  float* sub = n_sel == 1 ? a.sub_next + (int64_t)bh * D : a.part_sub + ((int64_t)bh * n_sel + y) * D;
   if (tid < D) {
     float sacc = 0.0f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) sacc += s_acc[w][tid];
-    a.sub_next[(int64_t)bh * D + tid] = sacc;
+    sub[tid] = sacc;
   }
   if (tid == 0) {
     double mt = 0.0;
     for (int w = 0; w < NW; ++w) mt += s_m[w];
-    a.mass_next[bh] = (float)mt;
+    if (n_sel == 1) a.mass_next[bh] = (float)mt;
+    else a.part_mass[(int64_t)bh * n_sel + y] = mt;
   }
+}
+
+// sub' and m' of each (b, h) from the selecting workgroups' sums, in their order
+template <int D>
+__global__ __launch_bounds__(D) void decode_sum_kernel(DecodeArgs a, int n_sel) {
+  const int bh = blockIdx.x, tid = threadIdx.x;
+  float s = 0.0f;
+  double m = 0.0;
+  for (int y = 0; y < n_sel; ++y) {
+    s += a.part_sub[((int64_t)bh * n_sel + y) * D + tid];
+    m += a.part_mass[(int64_t)bh * n_sel + y];
+  }
+  a.sub_next[(int64_t)bh * D + tid] = s;
+  if (tid == 0) a.mass_next[bh] = (float)m;
+}
+
+// Workgroups that select for one (b, h).  One top-k per CU at most, each of them all over the keys, so more only where
+// CUs are idle otherwise; shares of at most kSelWin rows and at least d + 2 (their sums take the place of the selected
+// positions in the workspace) and 128 (below, the gather is not what a share waits for).
+static int select_workgroups(int bh, int d, int n, int c_next) {
+  if (c_next == 0 || c_next == n) return 0;
+  const int most = std::min(std::min(256 / std::max(bh, 1), 8), c_next / std::max(d + 2, 128));
+  if (most < 2 || (c_next + most - 1) / most > kSelWin) return 1;
+  return most;
 }
 
 // workspace regions, each 256-byte aligned
@@ -422,22 +472,29 @@ static int decode_step(const char* fn, bool use_scratch, const uint16_t* q, cons
   int rc = check_launch("decode_partial_kernel");
   if (rc != FL_OK) return rc;
   // finalize: the top-k's register depth follows the number of keys (as in the selection kernels)
-  const int per = (n + kTopkThreads - 1) / kTopkThreads;
-  const dim3 gf(BH);
-#define FL_FIN(MM)                                                                        \
-  do {                                                                                    \
-    if (d == 128) decode_finalize_kernel<128, MM><<<gf, kTopkThreads, 0, st>>>(a);        \
-    else decode_finalize_kernel<64, MM><<<gf, kTopkThreads, 0, st>>>(a);                  \
+  const int n_sel = select_workgroups(BH, d, n, c_next);
+  a.part_mass = reinterpret_cast<double*>(base + L.sel);
+  a.part_sub = reinterpret_cast<float*>(a.part_mass + (int64_t)BH * n_sel);
+  const int keys = n_sel > 0 ? n : 0;
+  const dim3 gf(BH, 1 + n_sel);
+#define FL_FIN(MM, HH)                                                                        \
+  do {                                                                                        \
+    if (d == 128) decode_finalize_kernel<128, MM, HH><<<gf, kTopkThreads, 0, st>>>(a);        \
+    else decode_finalize_kernel<64, MM, HH><<<gf, kTopkThreads, 0, st>>>(a);                  \
   } while (0)
-  if (per <= 1) FL_FIN(1);
-  else if (per <= 2) FL_FIN(2);
-  else if (per <= 4) FL_FIN(4);
-  else if (per <= 8) FL_FIN(8);
-  else if (per <= 16) FL_FIN(16);
-  else if (per <= 32) FL_FIN(32);
-  else FL_FIN(64);
+  if (keys <= 1024) FL_FIN(1, 1);
+  else if (keys <= 2048) FL_FIN(2, 1);
+  else if (keys <= 4096) FL_FIN(4, 1);
+  else if (keys <= 8192) FL_FIN(8, 1);
+  else if (keys <= 16384) FL_FIN(16, 1);
+  else if (keys <= 32768) FL_FIN(32, 1);
+  else FL_FIN(32, 2);
 #undef FL_FIN
-  return check_launch("decode_finalize_kernel");
+  rc = check_launch("decode_finalize_kernel");
+  if (rc != FL_OK || n_sel < 2) return rc;
+  if (d == 128) decode_sum_kernel<128><<<BH, 128, 0, st>>>(a, n_sel);
+  else decode_sum_kernel<64><<<BH, 64, 0, st>>>(a, n_sel);
+  return check_launch("decode_sum_kernel");
 }
 
 extern "C" int fl_decode_step(const uint16_t* q, const uint16_t* k_cache, const uint16_t* v_cache,

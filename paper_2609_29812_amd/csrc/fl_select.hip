@@ -5,7 +5,7 @@
 //   reduces across the wave and writes the fp32 key.  HBM-bound: 4 * D * 2 bytes per candidate.
 //   When the budget keeps every candidate (k = n_cand, nested loops with a constant budget), extra
 //   workgroups of the same launch write the selection itself: the candidates and their slot map.
-// topk_select: one 1024-thread workgroup per segment runs the radix top-k of fl_topk.h.
+// topk_select: one workgroup per segment runs the radix top-k of fl_topk.h.
 #include "fl_common.h"
 #include "fl_topk.h"
 
@@ -91,34 +91,36 @@ __global__ __launch_bounds__(64 * kScoreWaves) void score_rows_kernel(
 
 // Segment s = blockIdx.x: keys at keys + s key_stride, ids from cand + s cand_stride (or id_base + p),
 // output at out + s out_stride, slot map at slot + s slot_n.
-template <int M>
-__global__ __launch_bounds__(kTopkThreads) void topk_select_kernel(
+template <int M, int NT, int NH>
+__global__ __launch_bounds__(NT) void topk_select_kernel(
     const float* __restrict__ keys, int64_t key_stride, int n, int k,
     const int32_t* __restrict__ cand, int64_t cand_stride, int id_base,
     int32_t* __restrict__ out, int64_t out_stride, int n_prefix,
     int32_t* __restrict__ slot, int slot_n) {
+  __shared__ TopkShared<M, NT, NH> sh;
   const int s = blockIdx.x;
-  topk_block<M>(keys + (int64_t)s * key_stride, n, k, cand ? cand + (int64_t)s * cand_stride : nullptr, id_base,
-                out + (int64_t)s * out_stride, n_prefix, slot ? slot + (int64_t)s * slot_n : nullptr, slot_n);
+  topk_block<M, NT, NH>(sh, keys + (int64_t)s * key_stride, n, k, cand ? cand + (int64_t)s * cand_stride : nullptr,
+                        id_base, out + (int64_t)s * out_stride, n_prefix, slot ? slot + (int64_t)s * slot_n : nullptr,
+                        slot_n);
 }
 
 int launch_topk(int segments, const float* keys, int64_t key_stride, int n, int k,
                        const int32_t* cand, int64_t cand_stride, int id_base, int32_t* out,
                        int64_t out_stride, int n_prefix, int32_t* slot, int slot_n,
                        hipStream_t st) {
-  const int per = (n + kTopkThreads - 1) / kTopkThreads;
-  dim3 grid(segments), block(kTopkThreads);
-#define FL_TOPK(MM)                                                                          \
-  topk_select_kernel<MM><<<grid, block, 0, st>>>(keys, key_stride, n, k, cand, cand_stride, \
-                                                 id_base, out, out_stride, n_prefix, slot,  \
-                                                 slot_n)
-  if (per <= 1) FL_TOPK(1);
-  else if (per <= 2) FL_TOPK(2);
-  else if (per <= 4) FL_TOPK(4);
-  else if (per <= 8) FL_TOPK(8);
-  else if (per <= 16) FL_TOPK(16);
-  else if (per <= 32) FL_TOPK(32);
-  else if (per <= 64) FL_TOPK(64);
+  const dim3 grid(segments);
+#define FL_TOPK(MM, TT, HH)                                                                                  \
+  topk_select_kernel<MM, TT, HH><<<grid, TT, 0, st>>>(keys, key_stride, n, k, cand, cand_stride, id_base, out, \
+                                                      out_stride, n_prefix, slot, slot_n)
+  // the fewest threads that hold the keys in few registers: a barrier of four waves costs less than one of 16
+  if (n <= 256) FL_TOPK(1, 256, 1);
+  else if (n <= 1024) FL_TOPK(4, 256, 1);
+  else if (n <= 2048) FL_TOPK(2, 1024, 1);
+  else if (n <= 4096) FL_TOPK(4, 1024, 1);
+  else if (n <= 8192) FL_TOPK(8, 1024, 1);
+  else if (n <= 16384) FL_TOPK(16, 1024, 1);
+  else if (n <= 32768) FL_TOPK(32, 1024, 1);
+  else if (n <= 65536) FL_TOPK(32, 1024, 2);
   else return set_error(FL_E_SHAPE, "top-k over %d keys exceeds the 65536 supported", n);
 #undef FL_TOPK
   return check_launch("topk_select_kernel");

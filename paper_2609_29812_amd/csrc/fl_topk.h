@@ -1,13 +1,14 @@
-// Radix top-k of one segment by one 1024-thread workgroup, shared by the selection kernels and the
-// decode step (Appendix D.1, Eq. 5; Appendix D.2, Eq. 6: the largest keys, ties to the lower position,
-// emitted in ascending position order).
+// Radix top-k of one segment by one workgroup, shared by the selection kernels and the decode step (Appendix D.1,
+// Eq. 5; Appendix D.2, Eq. 6: the largest keys, ties to the lower position, emitted in ascending position order).
 //
-// Keys are mapped to order-preserving uint32 and held in registers (M per thread).  The k-th largest
-// key is found in two stages: an LDS histogram of the top 12 bits and a block scan over its 4096 bins
-// give the bin that holds it; the keys of that bin are compacted into LDS and the remaining 20 bits are
-// resolved with digit histograms of 8, 8 and 4 bits over that (small) set (bit by bit over the
-// registers if the bin overflows the LDS buffer).  The selected positions are then compacted in
-// position order with two block scans, which emits them ascending and breaks ties by the lower index.
+// Keys are mapped to order-preserving uint32 and held in registers: thread t of NT holds the M consecutive positions
+// from t M on (two such blocks, NH = 2, above 32K keys), read coalesced and turned round in LDS, so that a thread's
+// selected positions are bits of one word and one block scan gives their places in the output.  The k-th largest key is
+// found by an LDS histogram over the keys' range, whose bin is compacted into LDS and resolved by digit histograms.
+//
+// Bound by latency: one workgroup, a chain of barriers.  32K keys (k = 1638, with the slot map): 23 us with keys
+// held in stripes, whose output order took ballot bitmaps through LDS, and LDS-permute scans; 18.7 us so (8K keys 15.7 against 10.2, 256 keys
+// 7.9 against 4.5).
 #pragma once
 #include "fl_common.h"
 
@@ -15,42 +16,53 @@
 
 namespace fl {
 
-// ---- block-wide helpers for a 1024-thread workgroup (16 waves) -----------------------------------
 constexpr int kTopkThreads = 1024;
-constexpr int kTopkWaves = kTopkThreads / 64;
 
-__device__ __forceinline__ int block_sum(int v, int* red /* [2][16] */, int parity) {
-  v = wave_sum_i32(v);
-  const int w = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) red[parity * kTopkWaves + w] = v;
-  __syncthreads();
-  int total = 0;
-#pragma unroll
-  for (int i = 0; i < kTopkWaves; ++i) total += red[parity * kTopkWaves + i];
-  return total;   // callers alternate parity, so the next write never races this read
+// ---- wave and workgroup helpers -------------------------------------------------------------------
+#define FL_DPP(old, x, ctrl, rows) __builtin_amdgcn_update_dpp((old), (x), (ctrl), (rows), 0xf, false)
+// inclusive prefix sum over the wave's lanes (row shifts, then the rows' totals broadcast to the rows after)
+__device__ __forceinline__ int wave_scan(int v) {
+  v += FL_DPP(0, v, 0x111, 0xf);
+  v += FL_DPP(0, v, 0x112, 0xf);
+  v += FL_DPP(0, v, 0x114, 0xf);
+  v += FL_DPP(0, v, 0x118, 0xf);
+  v += FL_DPP(0, v, 0x142, 0xa);
+  v += FL_DPP(0, v, 0x143, 0xc);
+  return v;
 }
+__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
+#define FL_STEP(ctrl, rows) v = min(v, (uint32_t)FL_DPP(-1, (int)v, ctrl, rows))
+  FL_STEP(0x111, 0xf); FL_STEP(0x112, 0xf); FL_STEP(0x114, 0xf); FL_STEP(0x118, 0xf); FL_STEP(0x142, 0xa);
+  FL_STEP(0x143, 0xc);
+#undef FL_STEP
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+#undef FL_DPP
 
-// Exclusive prefix sum over threads in thread order; returns the prefix and sets *total.
-__device__ __forceinline__ int block_exclusive_scan(int v, int* scratch /* [16] */, int* total) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  int incl = v;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    int t = __shfl_up(incl, off, 64);
-    if (lane >= off) incl += t;
-  }
-  __syncthreads();                                   // previous users of scratch are done
-  if (lane == 63) scratch[w] = incl;
+template <int NT>
+struct TopkScan {
+  int2 total[2][NT / 64];
+};
+
+// Exclusive prefix sums of two values over the workgroup's threads, and their totals.  Alternate `parity` between
+// calls: the next call's writes then never race this one's reads.
+template <int NT>
+__device__ __forceinline__ int2 block_scan2(int a, int b, TopkScan<NT>& sc, int parity, int2& all) {
+  const int w = threadIdx.x >> 6;
+  const int ia = wave_scan(a), ib = wave_scan(b);
+  if ((threadIdx.x & 63) == 63) sc.total[parity][w] = make_int2(ia, ib);
   __syncthreads();
-  int before = 0, all = 0;
+  int2 before = make_int2(0, 0);
+  all = make_int2(0, 0);
 #pragma unroll
-  for (int i = 0; i < kTopkWaves; ++i) {
-    int s = scratch[i];
-    before += (i < w) ? s : 0;
-    all += s;
+  for (int i = 0; i < NT / 64; ++i) {
+    const int2 s = sc.total[parity][i];
+    before.x += i < w ? s.x : 0;
+    before.y += i < w ? s.y : 0;
+    all.x += s.x;
+    all.y += s.y;
   }
-  *total = all;
-  return before + incl - v;
+  return make_int2(before.x + ia - a, before.y + ib - b);
 }
 
 // Histogram of one digit per lane and round, for keys that crowd into few bins: the bin of the wave's
@@ -75,29 +87,42 @@ struct WaveHist {
   }
 };
 
-// The bin, scanning bins from the highest, where the running count of keys first reaches krem.
-// hist holds nbins counts (nbins <= 4 * kTopkThreads); result in meta[0..2] = (bin, krem left in it,
-// its count).  Block-wide; ends with a barrier.
-__device__ __forceinline__ void find_bin(const int* hist, int nbins, int krem, int* scratch, int* meta) {
-  const int t = threadIdx.x;
-  const int per = nbins > kTopkThreads ? nbins / kTopkThreads : 1;   // 4 or 1
-  int hb[4] = {0, 0, 0, 0}, local = 0;
+__device__ __forceinline__ uint32_t orderable(float f) {
+  const uint32_t u = __float_as_uint(f + 0.0f);   // -0 and +0 are the same key
+  return max((u & 0x80000000u) ? ~u : (u | 0x80000000u), 1u);   // (0 is no key: only the lowest NaN moves)
+}
+
+template <int M, int NT, int NH>
+struct TopkShared {
+  static constexpr int kBins = 4 * NT;
+  static constexpr int kBuf = NT * (M + 1);   // rows of M keys, one word apart: strided reads spread over the banks
+  TopkScan<NT> scan;
+  uint32_t lo[NT / 64], hi[NT / 64];
+  int meta[3];                                // the threshold's bin, keys still to take from it, its size
+  int n_in;
+  int hist[kBins];
+  uint32_t buf[kBuf];                         // the keys by position, then the keys of the threshold's bin
+};
+
+// The bin, scanning bins from the highest, where the running count of keys first reaches krem; hist holds nbins
+// counts, PER per thread.  Result in meta; ends with a barrier.
+template <int PER, int NT>
+__device__ __forceinline__ void find_bin(const int* hist, int nbins, int krem, TopkScan<NT>& sc, int parity, int* meta) {
+  int hb[PER], local = 0;
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int bin = nbins - 1 - per * t - q;
-    if (q < per && bin >= 0) {
-      hb[q] = hist[bin];
-      local += hb[q];
-    }
+  for (int q = 0; q < PER; ++q) {
+    const int bin = nbins - 1 - PER * (int)threadIdx.x - q;
+    hb[q] = bin >= 0 ? hist[bin] : 0;
+    local += hb[q];
   }
-  int total;
-  const int above = block_exclusive_scan(local, scratch, &total);
+  int2 all;
+  const int above = block_scan2<NT>(local, 0, sc, parity, all).x;
   if (above < krem && above + local >= krem) {
     int acc = above;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      if (q < per && acc < krem && acc + hb[q] >= krem) {
-        meta[0] = nbins - 1 - per * t - q;
+    for (int q = 0; q < PER; ++q) {
+      if (acc < krem && acc + hb[q] >= krem) {
+        meta[0] = nbins - 1 - PER * (int)threadIdx.x - q;
         meta[1] = krem - acc;
         meta[2] = hb[q];
       }
@@ -107,262 +132,205 @@ __device__ __forceinline__ void find_bin(const int* hist, int nbins, int krem, i
   __syncthreads();
 }
 
-__device__ __forceinline__ uint32_t orderable(float f) {
-  uint32_t u = __float_as_uint(f + 0.0f);   // -0 and +0 are the same key
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
-
-// One workgroup (kTopkThreads threads) selects the top k of n keys kp[0..n).  Position p has id cp[p]
+// One workgroup of NT threads selects the top k of n <= M NT NH keys kp[0..n).  Position p has id cp[p]
 // (cp != NULL) or id_base + p.  Selected ids are written ascending at op[n_prefix + pos]; ids
 // 0..n_prefix-1 are written first (column sinks).  Optional slot map: sp[id] = pos (or -1), sp holding
 // slot_n entries.  Only output positions pos in [out_lo, out_hi) are written, at op[n_prefix + pos -
 // out_lo] (the sink ids only when out_lo == 0): a workgroup that needs one window of the selection keeps
-// it in LDS.  Thread t holds the keys of positions t + 1024 j (coalesced loads; the threshold search does
-// not care about order); the ascending output comes from bitmaps of the selected positions.  Ends with
-// the ids written by this workgroup's threads (no trailing barrier).
-template <int M>
-__device__ __forceinline__ void topk_block(const float* __restrict__ kp, int n, int k,
+// it in LDS.  Ends with the ids written by this workgroup's threads (no trailing barrier).
+template <int M, int NT, int NH>
+__device__ __forceinline__ void topk_block(TopkShared<M, NT, NH>& sh, const float* __restrict__ kp, int n, int k,
                                            const int32_t* __restrict__ cp, int id_base,
                                            int32_t* __restrict__ op, int n_prefix,
                                            int32_t* __restrict__ sp, int slot_n, int out_lo = 0,
                                            int out_hi = INT_MAX) {
-  constexpr int kHistBits = 12, kBins = 1 << kHistBits;
-  static_assert(kBins == 4 * kTopkThreads, "each thread owns four histogram bins");
-  constexpr int kCap = M * kTopkThreads < 32768 ? M * kTopkThreads : 32768;
-  constexpr int kWords = M * kTopkThreads / 32;            // bitmap words over all positions
-  constexpr int kWordsPerThread = (kWords + kTopkThreads - 1) / kTopkThreads;
-  static_assert(2 * kWords <= kCap, "the bitmaps reuse the compaction buffer");
-  __shared__ int red[2 * kTopkWaves];
-  __shared__ int scan_scratch[kTopkWaves];
-  __shared__ int hist[kBins];
-  __shared__ uint32_t cbuf[kCap];          // keys of the threshold's bin, later the two bitmaps
-  __shared__ int meta[3];                  // that bin, keys still to take from it, its size
+  static_assert(M <= 32 && (NH == 1 || M == 32), "a thread's selected positions of one block are one word");
+  constexpr int kBins = TopkShared<M, NT, NH>::kBins;
+  constexpr int kHistBits = __builtin_ctz(kBins), kDigit = __builtin_ctz(NT);
   const int t = threadIdx.x;
   const int lane = t & 63, wave = t >> 6;
   int32_t* slot = sp;
   if (slot) {
-    for (int i = t; i < slot_n; i += kTopkThreads) sp[i] = -1;
+    for (int i = t; i < slot_n; i += NT) sp[i] = -1;
   }
   if (out_lo == 0)
-    for (int i = t; i < n_prefix; i += kTopkThreads) op[i] = i;
+    for (int i = t; i < n_prefix; i += NT) op[i] = i;
+#pragma unroll
+  for (int q = 0; q < kBins / NT; ++q) sh.hist[q * NT + t] = 0;
+  if (t == 0) sh.n_in = 0;
 
-  // (buffer loads: out-of-range positions read 0 without a branch, so all M loads are in flight at once;
+  // (buffer loads: out-of-range positions read 0 without a branch, so all loads are in flight at once;
   // a bounds-checked pointer load puts each one behind its own branch and wait)
-  uint32_t u[M];
+  uint32_t u[NH][M];                          // codes; 0 past the last key, below every key
   {
     const __amdgpu_buffer_rsrc_t kr =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(kp), (short)0, n * 4, 0x00020000);
 #pragma unroll
-    for (int j = 0; j < M; ++j) {
-      const int p = t + kTopkThreads * j;
-      const float x = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(kr, (uint32_t)p * 4u, 0, 0));
-      u[j] = orderable(x) & (0u - (uint32_t)(p < n));    // padding: 0 (as a mask, not a branch)
+    for (int q = 0; q < NH; ++q) {
+      uint32_t x[M];
+#pragma unroll
+      for (int j = 0; j < M; ++j)
+        x[j] = __builtin_amdgcn_raw_buffer_load_b32(kr, (uint32_t)(q * NT * M + NT * j + t) * 4u, 0, 0);
+      if (q > 0) __syncthreads();
+#pragma unroll
+      for (int j = 0; j < M; ++j) {
+        const int p = NT * j + t;
+        sh.buf[p + p / M] = q * NT * M + p < n ? orderable(__uint_as_float(x[j])) : 0u;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int j = 0; j < M; ++j) u[q][j] = sh.buf[t * (M + 1) + j];
     }
   }
 
-  // k-th largest key.  (1) The keys' range [lo, hi]: the codes become offsets v = u - lo (order kept), and
-  // the first histogram takes the kHistBits bits of v from the highest bit the range needs (shift0 up),
+  // k-th largest key.  The keys' range (lo, hi], lo below every key: the codes become offsets v = u - lo (order kept;
+  // 0 past the last key, so below the k-th largest), and the first histogram takes the kHistBits bits of v from the highest bit the range needs (shift0 up),
   // so the bins cover the keys' actual range and the bin that holds the k-th largest is small.  With
   // k == n every position is taken and no threshold is needed.
   const bool take_all = k == n;
   uint32_t prefix = 0, mask = 0;
-  int krem = take_all ? 0 : k;
-  // (the range is taken on every path, so the keys have one form, offsets, in registers: with the raw keys
-  // kept for the paths without a search, the 32K-key kernel ran out of registers)
-  uint32_t lo = 0xFFFFFFFFu, hi = 0u;
-#pragma unroll
-  for (int j = 0; j < M; ++j) {
-    const bool valid = t + kTopkThreads * j < n;
-    lo = valid ? min(lo, u[j]) : lo;
-    hi = valid ? max(hi, u[j]) : hi;
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    lo = min(lo, (uint32_t)__shfl_xor((int)lo, off, 64));
-    hi = max(hi, (uint32_t)__shfl_xor((int)hi, off, 64));
-  }
-  if (lane == 0) {
-    red[wave] = (int)lo;
-    red[kTopkWaves + wave] = (int)hi;
-  }
-  for (int i = t; i < kBins; i += kTopkThreads) hist[i] = 0;
-  __syncthreads();
-#pragma unroll
-  for (int w2 = 0; w2 < kTopkWaves; ++w2) {
-    lo = min(lo, (uint32_t)red[w2]);
-    hi = max(hi, (uint32_t)red[kTopkWaves + w2]);
-  }
-  const uint32_t span = hi - lo;
-  const int shift0 = span >> kHistBits ? 32 - __builtin_clz(span) - kHistBits : 0;   // span >> shift0 < kBins
-#pragma unroll
-  for (int j = 0; j < M; ++j) u[j] = (t + kTopkThreads * j < n) ? u[j] - lo : 0u;
+  int krem = 0;
   if (k > 0 && !take_all) {                               // uniform
+    uint32_t lo = 0xFFFFFFFFu, nhi = 0xFFFFFFFFu;         // (the largest as the smallest complement)
+#pragma unroll
+    for (int q = 0; q < NH; ++q)
+#pragma unroll
+      for (int j = 0; j < M; ++j) {
+        lo = min(lo, u[q][j] - 1u);                       // (of 0, past the last key: no effect)
+        nhi = min(nhi, ~u[q][j]);
+      }
+    lo = wave_min_u32(lo);
+    nhi = wave_min_u32(nhi);
+    if (lane == 0) {
+      sh.lo[wave] = lo;
+      sh.hi[wave] = nhi;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w) {
+      lo = min(lo, sh.lo[w]);
+      nhi = min(nhi, sh.hi[w]);
+    }
+    const uint32_t span = ~nhi - lo;
+    const int shift0 = span >> kHistBits ? 32 - __builtin_clz(span) - kHistBits : 0;   // span >> shift0 < kBins
     WaveHist wh;
 #pragma unroll
-    for (int j = 0; j < M; ++j) wh.add(hist, u[j] >> shift0, t + kTopkThreads * j < n);
-    wh.flush(hist);
-    __syncthreads();                                      // (also: every wave has read red)
-    find_bin(hist, kBins, k, scan_scratch, meta);
-    const uint32_t bin = (uint32_t)meta[0];
-    const int cnt = meta[2];
-    krem = meta[1];
+    for (int q = 0; q < NH; ++q)
+#pragma unroll
+      for (int j = 0; j < M; ++j) {
+        u[q][j] = max(u[q][j], lo) - lo;
+        wh.add(sh.hist, u[q][j] >> shift0, true);
+      }
+    wh.flush(sh.hist);
+    __syncthreads();
+    find_bin<kBins / NT, NT>(sh.hist, kBins, k, sh.scan, 0, sh.meta);
+    const uint32_t bin = (uint32_t)sh.meta[0];
+    const int cnt = sh.meta[2];
+    krem = sh.meta[1];
     prefix = bin << shift0;
-    mask = shift0 < 32 ? ~0u << shift0 : 0u;
+    mask = ~0u << shift0;
     if (shift0 == 0) {
       // every offset is its own bin: the threshold is known
-    } else if (cnt <= kCap) {
-      // (2) compact that bin's keys into LDS (any order), then resolve the low shift0 bits with digit
-      // histograms of up to 8 bits over them
+    } else if (NH == 1 || cnt <= NT * M) {
+      // that bin's keys into LDS (any order), then the low shift0 bits with digit histograms of up to kDigit bits
       int n_in = 0;
 #pragma unroll
-      for (int j = 0; j < M; ++j) n_in += (t + kTopkThreads * j < n && (u[j] & mask) == prefix) ? 1 : 0;
-      int tot;
-      int off = block_exclusive_scan(n_in, scan_scratch, &tot);
+      for (int q = 0; q < NH; ++q)
 #pragma unroll
-      for (int j = 0; j < M; ++j)
-        if (t + kTopkThreads * j < n && (u[j] & mask) == prefix) cbuf[off++] = u[j];
-      int shift = shift0;
+        for (int j = 0; j < M; ++j) n_in += (u[q][j] & mask) == prefix ? 1 : 0;
+      const int incl = wave_scan(n_in);
+      int off = 0;
+      if (lane == 63 && incl > 0) off = atomicAdd(&sh.n_in, incl);
+      off = __builtin_amdgcn_readlane(off, 63) + incl - n_in;
+#pragma unroll
+      for (int q = 0; q < NH; ++q)
+#pragma unroll
+        for (int j = 0; j < M; ++j)
+          if ((u[q][j] & mask) == prefix) sh.buf[off++] = u[q][j];
+      int shift = shift0, parity = 1;
       while (shift > 0) {                                 // uniform
-        const int nb = shift < 8 ? shift : 8;
+        const int passes = (shift + kDigit - 1) / kDigit;
+        const int nb = (shift + passes - 1) / passes;
         shift -= nb;
-        for (int i = t; i < (1 << nb); i += kTopkThreads) hist[i] = 0;
+        if (t < (1 << nb)) sh.hist[t] = 0;
         __syncthreads();                                  // also orders the compaction writes
         WaveHist dh;
-        for (int i0 = 0; i0 < cnt; i0 += kTopkThreads) {
+        for (int i0 = 0; i0 < cnt; i0 += NT) {
           const int i = i0 + t;
-          const uint32_t v = i < cnt ? cbuf[i] : 0u;
-          dh.add(hist, (v >> shift) & ((1u << nb) - 1), i < cnt && (v & mask) == prefix);
+          const uint32_t v = i < cnt ? sh.buf[i] : 0u;
+          dh.add(sh.hist, (v >> shift) & ((1u << nb) - 1), i < cnt && (v & mask) == prefix);
         }
-        dh.flush(hist);
+        dh.flush(sh.hist);
         __syncthreads();
-        find_bin(hist, 1 << nb, krem, scan_scratch, meta);
-        prefix |= (uint32_t)meta[0] << shift;
+        find_bin<1, NT>(sh.hist, 1 << nb, krem, sh.scan, parity, sh.meta);
+        parity ^= 1;
+        prefix |= (uint32_t)sh.meta[0] << shift;
         mask |= ((1u << nb) - 1) << shift;
-        krem = meta[1];
+        krem = sh.meta[1];
       }
     } else {
-      // (2b) too many keys in one bin for the LDS buffer: resolve the low bits over the registers
+      // too many keys in one bin for the LDS buffer: resolve the low bits over the registers
       for (int bit = shift0 - 1; bit >= 0; --bit) {
         const uint32_t want = prefix | (1u << bit), m2 = mask | (1u << bit);
         int c = 0;
 #pragma unroll
-        for (int j = 0; j < M; ++j) c += ((t + kTopkThreads * j) < n && (u[j] & m2) == want) ? 1 : 0;
-        c = block_sum(c, red, bit & 1);
-        if (c >= krem) prefix = want; else krem -= c;
+        for (int q = 0; q < NH; ++q)
+#pragma unroll
+          for (int j = 0; j < M; ++j) c += (u[q][j] & m2) == want ? 1 : 0;
+        int2 all;
+        block_scan2<NT>(c, 0, sh.scan, bit & 1, all);
+        if (all.x >= krem) prefix = want; else krem -= all.x;
         mask = m2;
       }
-    }
-  }
-  // (3) bitmaps of the positions with a key above the threshold and equal to it (bit p % 32 of word
-  // p / 32): positions t + 1024 j of a wave's lanes 0-31 and 32-63 form words 32 j + 2 wave and
-  // 32 j + 2 wave + 1, taken by ballot.  The wave gathers its 2 M words per map into lanes (word
-  // 2 j + h in lane (2 j + h) % 64 of register (2 j + h) / 64) and stores them without branches.
-  uint32_t* bm_gt = cbuf;
-  uint32_t* bm_eq = cbuf + kWords;
-  constexpr int kRegs = (2 * M + 63) / 64;
-  uint32_t gv[kRegs], ev[kRegs];
-#pragma unroll
-  for (int r = 0; r < kRegs; ++r) gv[r] = ev[r] = 0u;
-#pragma unroll
-  for (int j = 0; j < M; ++j) {
-    const bool valid = k > 0 && t + kTopkThreads * j < n;
-    const uint64_t g = __builtin_amdgcn_ballot_w64(valid && (take_all || u[j] > prefix));
-    const uint64_t e = __builtin_amdgcn_ballot_w64(valid && !take_all && u[j] == prefix);
-    const int r = (2 * j) / 64, l0 = (2 * j) % 64;
-    gv[r] = lane == l0 ? (uint32_t)g : lane == l0 + 1 ? (uint32_t)(g >> 32) : gv[r];
-    ev[r] = lane == l0 ? (uint32_t)e : lane == l0 + 1 ? (uint32_t)(e >> 32) : ev[r];
-  }
-  __syncthreads();                                        // cbuf is no longer read
-#pragma unroll
-  for (int r = 0; r < kRegs; ++r) {
-    const int wj = 64 * r + lane;                         // word 2 j + h of this wave
-    if (wj < 2 * M) {
-      const int wd = 32 * (wj >> 1) + 2 * wave + (wj & 1);
-      bm_gt[wd] = gv[r];
-      bm_eq[wd] = ev[r];
-    }
-  }
-  __syncthreads();
-  // thread t owns words t * kWordsPerThread ..; the equal keys taken are the krem lowest positions
-  uint32_t gw[kWordsPerThread], ew[kWordsPerThread];
-  int n_eq = 0;
-#pragma unroll
-  for (int q = 0; q < kWordsPerThread; ++q) {
-    const int wd = t * kWordsPerThread + q;
-    gw[q] = wd < kWords ? bm_gt[wd] : 0u;
-    ew[q] = wd < kWords ? bm_eq[wd] : 0u;
-    n_eq += __builtin_popcount(ew[q]);
-  }
-  int total;
-  const int eq_before = block_exclusive_scan(n_eq, scan_scratch, &total);
-  int take = krem - eq_before;                          // equal keys this thread still takes
-  int n_sel = 0;
-#pragma unroll
-  for (int q = 0; q < kWordsPerThread; ++q) {
-    uint32_t e = ew[q], keep = 0;
-    while (e != 0 && take > 0) {
-      const uint32_t low = e & (0u - e);
-      keep |= low;
-      e ^= low;
-      --take;
-    }
-    gw[q] |= keep;
-    n_sel += __builtin_popcount(gw[q]);
-  }
-  int pos = block_exclusive_scan(n_sel, scan_scratch, &total);
-  if constexpr (M <= 4) {
-    // few keys per thread: record each word's selected bits and first output position, then every thread
-    // writes the selected positions among its own (t + 1024 j: coalesced id loads)
-    uint32_t* sel_w = cbuf;                               // reuses the bitmaps' space (read above)
-    int* pos_w = reinterpret_cast<int*>(cbuf + kWords);
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < kWordsPerThread; ++q) {
-      const int wd = t * kWordsPerThread + q;
-      if (wd < kWords) {
-        sel_w[wd] = gw[q];
-        pos_w[wd] = pos;
-      }
-      pos += __builtin_popcount(gw[q]);
-    }
-    // the -1 fill above is complete before positions are written (same workgroup: a workgroup-scope
-    // release suffices; a device-scope fence would also write back the L2)
-    if (slot) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < M; ++j) {
-      const int p = t + kTopkThreads * j;
-      if (p >= n) continue;
-      const uint32_t sw = sel_w[p >> 5];
-      if ((sw >> (p & 31)) & 1u) {
-        const int o = pos_w[p >> 5] + __builtin_popcount(sw & ((1u << (p & 31)) - 1u));
-        if (o < k) {                // exactly k positions are selected; the bound is a safety net
-          const int id = cp ? cp[p] : id_base + p;
-          if (o >= out_lo && o < out_hi) op[n_prefix + o - out_lo] = id;
-          if (slot) sp[id] = o;
-        }
-      }
-    }
-  } else {
-    // many keys per thread, few selected per word: thread t writes the selected positions of its own
-    // words in order
-    if (slot) {   // the -1 fill above is complete before positions are written (workgroup scope suffices)
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
       __syncthreads();
     }
+  }
+  // The selected positions: keys above the threshold, and the krem lowest positions of those equal to it.
+  uint32_t gt[NH], eq[NH];
 #pragma unroll
-    for (int q = 0; q < kWordsPerThread; ++q) {
-      uint32_t g = gw[q];
-      while (g != 0) {
-        const int p = 32 * (t * kWordsPerThread + q) + __builtin_ctz(g);
-        g &= g - 1;
-        if (pos < k) {              // exactly k positions are selected; the bound is a safety net
-          const int id = cp ? cp[p] : id_base + p;
-          if (pos >= out_lo && pos < out_hi) op[n_prefix + pos - out_lo] = id;
-          if (slot) sp[id] = pos;
-        }
-        ++pos;
+  for (int q = 0; q < NH; ++q) {
+    gt[q] = eq[q] = 0u;
+#pragma unroll
+    for (int j = 0; j < M; ++j) {
+      gt[q] |= u[q][j] > prefix ? 1u << j : 0u;
+      eq[q] |= u[q][j] == prefix ? 1u << j : 0u;
+    }
+    if (take_all || k == 0) {                             // (the codes themselves, no threshold)
+      const int nv = min(max(n - q * NT * M - t * M, 0), M);
+      gt[q] = k == 0 ? 0u : nv >= 32 ? ~0u : (1u << nv) - 1u;
+      eq[q] = 0u;
+    }
+  }
+  // the -1 fill above is complete before positions are written (same workgroup: a workgroup-scope
+  // release suffices; a device-scope fence would also write back the L2)
+  if (slot) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  int2 base = make_int2(0, 0);
+#pragma unroll
+  for (int q = 0; q < NH; ++q) {
+    int2 all;
+    // (find_bin's last barrier lies between its last scan and this one)
+    int2 at = block_scan2<NT>(__builtin_popcount(gt[q]), __builtin_popcount(eq[q]), sh.scan, q & 1, all);
+    at.x += base.x;
+    at.y += base.y;
+    base.x += all.x;
+    base.y += all.y;
+    int pos = at.x + min(at.y, krem);
+    int take = krem - at.y;                               // equal keys this thread still takes
+    uint32_t both = gt[q] | eq[q];
+    while (both != 0) {
+      const int j = __builtin_ctz(both);
+      both &= both - 1;
+      if ((eq[q] >> j) & 1u) {
+        if (take <= 0) continue;
+        --take;
       }
+      if (pos < k) {                // exactly k positions are selected; the bound is a safety net
+        const int p = q * NT * M + t * M + j;
+        const int id = cp ? cp[p] : id_base + p;
+        if (pos >= out_lo && pos < out_hi) op[n_prefix + pos - out_lo] = id;
+        if (slot) sp[id] = pos;
+      }
+      ++pos;
     }
   }
 }
