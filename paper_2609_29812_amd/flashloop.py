@@ -114,16 +114,19 @@ def _check(rc: int, fn: str):
         raise FlashLoopError(f"{fn}: {lib.fl_status_str(rc).decode()}: {lib.fl_last_error().decode()}")
 
 
+# The calls below run on the host between launches of a few microseconds each, so the marshalling is kept short:
+# pointers as plain integers (c_void_p arguments take them), the stream by one C call instead of the Stream object
+# (5 us of a call's 16), and a tensor that passes its checks passes them in one expression.
 def _p(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _dev(t, dtype, name, shape=None):
-    if t is None:
+    if t is None or (t.dtype is dtype and t.is_cuda and t.is_contiguous() and (shape is None or t.shape == shape)):
         return
     if not t.is_cuda:
         raise FlashLoopError(f"{name} must be a device tensor")
@@ -139,10 +142,11 @@ def _dev(t, dtype, name, shape=None):
 def select_tokens(k_cur, k_prev, v_cur, v_prev, k, cand=None, normalize=True, eps=1e-6, slot=True,
                   out_key=None, out_idx=None, out_slot=None):
     """Active rows of the loop: returns (idx int32 [B, k], slot int32 [B, N] or None, key fp32 [B, n])."""
-    B, N = k_cur.shape[:2]
+    shape = k_cur.shape
+    B, N = shape[:2]
     D = k_cur.numel() // (B * N)
     for name, t in (("k_cur", k_cur), ("k_prev", k_prev), ("v_cur", v_cur), ("v_prev", v_prev)):
-        _dev(t, torch.bfloat16, name, None if t is None else k_cur.shape)
+        _dev(t, torch.bfloat16, name, shape)
     n_cand = N if cand is None else cand.shape[1]
     _dev(cand, torch.int32, "cand", None if cand is None else (B, n_cand))
     dev = k_cur.device
@@ -220,11 +224,11 @@ def kv_residual_quant_kv(k_cur, k_ref, v_cur, v_ref, idx, bits, group, mode=DQ_C
     COMMIT: rows idx of k_ref / v_ref are updated in place and the rows entries are None; with v_f16 (fp16
     [B, N, H, d], COMMIT only) its rows idx receive the fp16 copy of the updated values
     (fl_kv_residual_quant_kv_v16)."""
-    B, N, H, d = k_cur.shape
+    B, N, H, d = shape = k_cur.shape
     _dev(k_cur, torch.bfloat16, "k_cur")
-    _dev(v_cur, torch.bfloat16, "v_cur", k_cur.shape)
-    _dev(k_ref, torch.bfloat16, "k_ref", k_cur.shape)
-    _dev(v_ref, torch.bfloat16, "v_ref", k_cur.shape)
+    _dev(v_cur, torch.bfloat16, "v_cur", shape)
+    _dev(k_ref, torch.bfloat16, "k_ref", shape)
+    _dev(v_ref, torch.bfloat16, "v_ref", shape)
     k = N if idx is None else idx.shape[1]
     _dev(idx, torch.int32, "idx", None if idx is None else (B, k))
     dev = k_cur.device
@@ -234,8 +238,8 @@ def kv_residual_quant_kv(k_cur, k_ref, v_cur, v_ref, idx, bits, group, mode=DQ_C
         scale = zero = None
         if bits != 16:
             shp = meta_shape(B, k, H, d, group, axis)
-            scale = torch.empty(shp, dtype=torch.float16, device=dev)
-            zero = torch.empty(shp, dtype=torch.float16, device=dev)
+            scale = torch.empty(*shp, dtype=torch.float16, device=dev)
+            zero = torch.empty_like(scale)
         out_rows = None
         if mode == DQ_COMPACT and rows:
             out_rows = torch.empty(B, k, H, d, dtype=torch.bfloat16, device=dev)
@@ -327,33 +331,34 @@ def loop_sparse_attn(q_cur, q_prev, k_cache, v_cache, k_new, v_new, slot, rows, 
     slot_prev (the previous loop's slot map) reuse the previous loop's add terms as the subtract terms, in
     which case q_prev may be None, and k_new/v_new may be None when the caches already hold this loop's rows.
     v16: the fp16 copy of v_cache (given terms over current caches only; fl_loop_sparse_attn_terms_v16)."""
-    B, N, H, d = q_cur.shape
+    B, N, H, d = shape = q_cur.shape
     k = rows.shape[1]
+    packed = (B, k, H, d)
     reuse = term_prev is not None
     for name, t in (("q_cur", q_cur), ("q_prev", q_prev), ("k_cache", k_cache), ("v_cache", v_cache)):
-        _dev(t, torch.bfloat16, name, q_cur.shape)
-    _dev(k_new, torch.bfloat16, "k_new", (B, k, H, d))
-    _dev(v_new, torch.bfloat16, "v_new", (B, k, H, d))
+        _dev(t, torch.bfloat16, name, shape)
+    _dev(k_new, torch.bfloat16, "k_new", packed)
+    _dev(v_new, torch.bfloat16, "v_new", packed)
     _dev(slot, torch.int32, "slot", (B, N))
     _dev(rows, torch.int32, "rows", (B, k))
     c_list = 0 if cols is None else cols.shape[2]
     _dev(cols, torch.int32, "cols", None if cols is None else (B, H, c_list))
     _dev(lse_ref, torch.float32, "lse_ref", (B, N, H))
-    _dev(o, torch.float32, "o", (B, N, H, d))
+    _dev(o, torch.float32, "o", shape)
     k_prev = 0
     if reuse:
         k_prev = term_prev.shape[1]
         _dev(term_prev, torch.float32, "term_prev", (B, k_prev, H, d))
         _dev(mass_prev, torch.float32, "mass_prev", (B, k_prev, H))
         _dev(slot_prev, torch.int32, "slot_prev", (B, N))
-    _dev(term_out, torch.float32, "term_out", (B, k, H, d))
+    _dev(term_out, torch.float32, "term_out", packed)
     _dev(mass_out, torch.float32, "mass_out", (B, k, H))
     sm_scale = 1.0 / math.sqrt(d) if sm_scale is None else sm_scale
     lib = load()
     if v16 is not None:
         if not reuse or k_new is not None or v_new is not None:
             raise FlashLoopError("loop_sparse_attn: v16 needs term_prev and current caches (k_new = v_new = None)")
-        _dev(v16, torch.float16, "v16", q_cur.shape)
+        _dev(v16, torch.float16, "v16", shape)
         rc = lib.fl_loop_sparse_attn_terms_v16(_p(q_cur), _p(k_cache), _p(v_cache), _p(v16), _p(rows), k, _p(cols),
                                                c_list, window, B, N, H, d, sm_scale, _p(lse_ref), _p(o),
                                                _p(term_prev), _p(mass_prev), _p(slot_prev), k_prev, _p(term_out),
@@ -394,10 +399,10 @@ def subtract_terms(q_prev, k_cache, v_cache, rows, cols, window, lse_ref, term_o
     """Subtract term and mass of Eq. 7 over the previous loop's state: (term fp32 [B, k, H, d], m fp32 [B, k, H])
     in the row order of `rows` (fl_loop_subtract_terms; with v16, the fp16 copy of v_cache,
     fl_loop_subtract_terms_v16)."""
-    B, N, H, d = q_prev.shape
+    B, N, H, d = shape = q_prev.shape
     k = rows.shape[1]
     for name, t in (("q_prev", q_prev), ("k_cache", k_cache), ("v_cache", v_cache)):
-        _dev(t, torch.bfloat16, name, q_prev.shape)
+        _dev(t, torch.bfloat16, name, shape)
     _dev(rows, torch.int32, "rows", (B, k))
     c_list = 0 if cols is None else cols.shape[2]
     _dev(cols, torch.int32, "cols", None if cols is None else (B, H, c_list))
@@ -408,7 +413,7 @@ def subtract_terms(q_prev, k_cache, v_cache, rows, cols, window, lse_ref, term_o
     _dev(mass_out, torch.float32, "mass_out", (B, k, H))
     sm_scale = 1.0 / math.sqrt(d) if sm_scale is None else sm_scale
     if v16 is not None:
-        _dev(v16, torch.float16, "v16", q_prev.shape)
+        _dev(v16, torch.float16, "v16", shape)
         rc = load().fl_loop_subtract_terms_v16(_p(q_prev), _p(k_cache), _p(v_cache), _p(v16), _p(rows), k, _p(cols),
                                                c_list, window, B, N, H, d, sm_scale, _p(lse_ref), _p(term_out),
                                                _p(mass_out), _stream())
