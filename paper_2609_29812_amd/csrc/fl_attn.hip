@@ -1,5 +1,5 @@
-// Mass-corrected sparse attention update (Sections 3.2 and 4.2, Eq. 3; Appendix D.2, Eq. 7) and the
-// dense source loop (Eq. 2, causal).
+// Mass-corrected sparse attention update (Sections 3.2 and 4.2, Eq. 3; Appendix D.2, Eq. 7), and the entry points of
+// the attention calls (the dense source loop's kernel is in fl_dense_attn.hip, the segment kernels in fl_seg_attn.hip).
 //
 // Column sets.  For updated row i the columns are S_i = (list U band(i)) restricted to j <= i; a column
 // in both is counted once by giving list columns the condition j + window <= i and band columns
@@ -10,11 +10,9 @@
 //   phase B  band columns, cache state      subtract: all; add: columns not updated this loop
 //   phase C  updated list columns, new rows add only (compacted per (batch, head) by a prep kernel)
 //   phase D  updated band columns, new rows add only (a contiguous range of the active rows)
-// The dense loop is phase B alone with an unbounded band.
 //
-// Work decomposition.  A workgroup of 4 waves takes consecutive updated rows of one (batch, head): 64
-// rows in the sparse update, where waves 0-1 run the subtract pass and waves 2-3 the add pass for the
-// same two groups of 32 rows, and 128 rows in the dense loop, where every wave runs the softmax pass.
+// Work decomposition.  A workgroup of 4 waves takes 64 consecutive updated rows of one (batch, head): waves 0-1
+// run the subtract pass and waves 2-3 the add pass for the same two groups of 32 rows.
 // When the subtract term is the previous loop's stored add term (loops >= 3), reuse_attn_kernel runs the
 // add pass alone with one 16-row group per wave.  The row tiles of one (batch, head) map to one XCD so
 // its list columns stay in that XCD's L2.
@@ -65,13 +63,10 @@ struct AttnArgs {
   float pinf;                // +inf
 };
 
-// MODE: kDense (loop 1, every row over all causal columns) or kFull (a sparse loop with both passes).
-constexpr int kDense = 0, kFull = 1;
-
-template <int D, int MODE>
+// A sparse loop with both passes.
+template <int D>
 __global__ __launch_bounds__(256, 2) void loop_attn_kernel(AttnArgs a) {
-  constexpr bool DENSE = MODE == kDense;
-  constexpr int GROUPS = DENSE ? 4 : 2;
+  constexpr int GROUPS = 2;
   constexpr int BM = 32 * GROUPS;
   constexpr int KS = D / 16;              // k-steps of QK^T
   constexpr int DB = D / 32;              // 32-dim output blocks
@@ -81,7 +76,7 @@ __global__ __launch_bounds__(256, 2) void loop_attn_kernel(AttnArgs a) {
   constexpr int INST_PER_WAVE = INST_PER_TILE / 4;   // per tensor (K and V each)
   __shared__ Slot<D> s0, s1, s2, s3;
   // tables of tile v in entry v % 8, written by two 64-lane stores with no branch:
-  //   [0, kBN)        column ids, plain (dense loop, subtract pass; kPad = padding)
+  //   [0, kBN)        column ids, plain (subtract pass; kPad = padding)
   //   [kBN, 2 kBN)    column ids for the add pass, where the columns updated this loop are padding
   //   [2 kBN, 3 kBN)  byte offset of each column's row in its source (kOOB: none)
   //   [3 kBN, 4 kBN)  whether some column of the tile was updated this loop (every entry the same)
@@ -94,7 +89,7 @@ __global__ __launch_bounds__(256, 2) void loop_attn_kernel(AttnArgs a) {
   const int hw = lane >> 5;
   const int r32 = lane & 31;
   const int group = wave % GROUPS;
-  const bool add_pass = MODE != kFull || wave >= 2;
+  const bool add_pass = wave >= 2;
 
   // work item -> (batch*head, row tile); the row tiles of one (batch, head) stay on one XCD
   const int n_rt = (a.k + BM - 1) / BM;
@@ -110,8 +105,8 @@ __global__ __launch_bounds__(256, 2) void loop_attn_kernel(AttnArgs a) {
   }
   const int b = bh / a.H, h = bh % a.H;
   const int64_t HD = (int64_t)a.H * D;
-  const int32_t* rowp = DENSE ? nullptr : a.rows + (int64_t)b * a.k;
-  auto row_of = [&](int p) { return DENSE ? p : rowp[p]; };
+  const int32_t* rowp = a.rows + (int64_t)b * a.k;
+  auto row_of = [&](int p) { return rowp[p]; };
 
   const int p0 = rt * BM;
   const int last_p = min(p0 + BM, a.k) - 1;
@@ -136,18 +131,18 @@ __global__ __launch_bounds__(256, 2) void loop_attn_kernel(AttnArgs a) {
     }
   }
   float lse2 = 0.0f;
-  if (!DENSE && !add_pass && row_ok) lse2 = a.lse_ref[((int64_t)b * a.N + row_i) * a.H + h] * 1.4426950408889634f;
+  if (!add_pass && row_ok) lse2 = a.lse_ref[((int64_t)b * a.N + row_i) * a.H + h] * 1.4426950408889634f;
 
   // ---- phase extents (uniform) ----------------------------------------------------------------------
   const int recA = bh * a.c_list;                  // record offsets of the four phases
   const int recC = a.off_upd + bh * a.c_list;
   const int recB = a.off_band + b * a.N;
   const int recD = a.off_rows + b * a.k;
-  const int2* descp = DENSE ? nullptr : a.rec + recA;
-  const int2* updp = DENSE ? nullptr : a.rec + recC;
+  const int2* descp = a.rec + recA;
+  const int2* updp = a.rec + recC;
   if (tid < 2) {
     int n = 0;
-    if (!DENSE && a.c_list > 0) {
+    if (a.c_list > 0) {
       // tid 0: list entries with j + window <= max_row; tid 1: the same among the updated entries
       const int2* lp = tid == 0 ? descp : updp;
       const int len = tid == 0 ? a.c_list : a.n_upd[(int64_t)b * a.H + h];
@@ -162,12 +157,12 @@ __global__ __launch_bounds__(256, 2) void loop_attn_kernel(AttnArgs a) {
     s_meta[tid] = n;
   }
   // band extent of the workgroup's rows
-  const int bandLo = DENSE ? 0 : (a.window > 0 ? max(0, min_row - a.window + 1) : 0);
-  const int bandHi = DENSE ? max_row : (a.window > 0 ? max_row : -1);
+  const int bandLo = a.window > 0 ? max(0, min_row - a.window + 1) : 0;
+  const int bandHi = a.window > 0 ? max_row : -1;
   // phase D: the active rows inside [bandLo, bandHi] are a contiguous range of the sorted row list,
   // ending with this tile's last row
   int pa = 0, pb = 0;
-  if (!DENSE && a.window > 0) {
+  if (a.window > 0) {
     int lo = 0, hi = a.k;
     while (lo < hi) {
       const int mid = (lo + hi) >> 1;
@@ -196,10 +191,9 @@ __global__ __launch_bounds__(256, 2) void loop_attn_kernel(AttnArgs a) {
   // a sentinel (kPad, -1).  Records are loaded eight tiles ahead and four steps later turned into the LDS
   // tables of entry v % 8: column ids for the masks and the byte offset of the row the DMA reads.
   const int c32 = lane & 31;
-  const rsrc_t recR = make_rsrc(DENSE ? (const void*)a.k_cache : (const void*)a.rec, DENSE ? 0u : a.rec_bytes);
+  const rsrc_t recR = make_rsrc(a.rec, a.rec_bytes);
   const uint32_t sentinel = (uint32_t)a.off_sent * 8u;
   auto load_desc = [=](int v) -> u32x2 {
-    if constexpr (DENSE) return u32x2{0u, 0u};
     const bool inA = v < tA, inB = v < n_old, inC = v < n_old + tC;   // uniform
     const int start = inA ? 0 : inB ? tA : inC ? n_old : n_old + tC;
     const int base = inA ? recA : inB ? recB + bandLo : inC ? recC : recD + pa;
@@ -212,24 +206,12 @@ __global__ __launch_bounds__(256, 2) void loop_attn_kernel(AttnArgs a) {
   // buffer descriptors of the K/V tensors of this batch element
   const uint32_t rb = (uint32_t)(HD * 2);
   const uint32_t head_off = (uint32_t)(h * D * 2);
-  const rsrc_t kcR = make_rsrc(a.k_cache + (int64_t)b * a.N * HD, (uint32_t)a.N * rb);
-  const rsrc_t vcR = make_rsrc(a.v_cache + (int64_t)b * a.N * HD, (uint32_t)a.N * rb);
-
   auto store_desc = [=](int v, u32x2 w) {
-    int cid, row;
-    bool upd;
-    if constexpr (DENSE) {
-      cid = v * kBN + c32;                 // the band from column 0
-      if (cid > bandHi) cid = kPad;
-      row = cid;
-      upd = false;
-    } else {
-      const bool newer = v >= n_old;
-      cid = (int)w[0];
-      const int aux = (int)w[1];
-      upd = !newer && aux >= 0;            // updated this loop but staged from the cache
-      row = newer ? aux : cid;
-    }
+    const bool newer = v >= n_old;
+    const int cid = (int)w[0];
+    const int aux = (int)w[1];
+    const bool upd = !newer && aux >= 0;   // updated this loop but staged from the cache
+    const int row = newer ? aux : cid;
     const bool valid = cid != kPad;
     // lanes 0-31 hold the records; lanes 32-63 take their add-view ids across the half-swap
     const uint32_t cid_add = upd ? (uint32_t)kPad : (uint32_t)cid;
@@ -240,23 +222,16 @@ __global__ __launch_bounds__(256, 2) void loop_attn_kernel(AttnArgs a) {
     tab[v & 7][2 * kBN + lane] = lane < kBN ? off : (uint32_t)(any != 0);
   };
 
-  // LDS-DMA of tile u into slot sl: each wave issues INST_PER_WAVE K and INST_PER_WAVE V instructions,
-  // always (padding and tiles past the end load nothing: their offsets are out of range)
-  // DMA plan: every wave issues NI = 2 * INST_PER_WAVE one-kilobyte instructions per tile.  In the
-  // sparse update the subtract waves (0-1) load all of V and convert it, the add waves (2-3) load all
-  // of K; in the dense loop every wave loads its share of both.  inst_of(t) is the instruction (row
-  // block of the tile) of the wave's t-th op, is_v_op(t) whether it targets V.
+  // LDS-DMA of tile u into slot sl: every wave issues NI one-kilobyte instructions per tile, always (padding and
+  // tiles past the end load nothing: their offsets are out of range).  The subtract waves (0-1) load all of V and
+  // convert it, the add waves (2-3) load all of K; inst_of(t) is the instruction (row block of the tile) of the wave's
+  // t-th op.
   constexpr int NI = 2 * INST_PER_WAVE;
-  constexpr bool SPLIT_KV = MODE == kFull;
-  const bool v_wave = SPLIT_KV && __builtin_amdgcn_readfirstlane(wave) < 2;
-  // the sparse update's per-wave source tensors (cache state and new rows)
+  const bool v_wave = __builtin_amdgcn_readfirstlane(wave) < 2;
+  // the wave's source tensors (cache state and new rows)
   const rsrc_t srcC = make_rsrc((v_wave ? a.v_cache : a.k_cache) + (int64_t)b * a.N * HD, (uint32_t)a.N * rb);
-  const rsrc_t srcN = make_rsrc(DENSE ? a.k_cache : (v_wave ? a.v_new : a.k_new) + (int64_t)b * a.k * HD,
-                                DENSE ? 0u : (uint32_t)a.k * rb);
-  const rsrc_t knR = make_rsrc(DENSE ? a.k_cache : a.k_new + (int64_t)b * a.k * HD, DENSE ? 0u : (uint32_t)a.k * rb);
-  const rsrc_t vnR = make_rsrc(DENSE ? a.v_cache : a.v_new + (int64_t)b * a.k * HD, DENSE ? 0u : (uint32_t)a.k * rb);
-  auto inst_of = [=](int t) { return SPLIT_KV ? (wave & 1) * NI + t : wave * INST_PER_WAVE + (t % INST_PER_WAVE); };
-  auto is_v_op = [=](int t) { return SPLIT_KV ? v_wave : t >= INST_PER_WAVE; };
+  const rsrc_t srcN = make_rsrc((v_wave ? a.v_new : a.k_new) + (int64_t)b * a.k * HD, (uint32_t)a.k * rb);
+  auto inst_of = [=](int t) { return (wave & 1) * NI + t; };
   // source byte offsets of this lane's chunks of tile u (read from the tables ahead of the barrier)
   struct Offs { uint32_t o[NI]; };
   auto tile_offs = [=](int u) {
@@ -271,43 +246,18 @@ __global__ __launch_bounds__(256, 2) void loop_attn_kernel(AttnArgs a) {
   // (each offset goes through a local: handing the struct member straight to the builtin makes the
   // host compilation drop the kernel's launch stub)
   auto issue = [=](int u, Slot<D>& sl, const Offs& of) {
-    if constexpr (!SPLIT_KV) {
-      const bool newer = !DENSE && u >= n_old;   // uniform: one of two scalar branches, same op count
-      if (newer) {
+    uint16_t* dst = v_wave ? sl.v : sl.k;
+    if (u >= n_old) {                     // uniform: one of two scalar branches, same op count
 #pragma unroll
-        for (int t = 0; t < NI; ++t) {
-          const int inst = inst_of(t);
-          const uint32_t off = of.o[t];
-          if (t < INST_PER_WAVE)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(knR, FL_LDS(sl.k + inst * 512), 16, off, 0, 0, kDmaPolicy);
-          else
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(vnR, FL_LDS(sl.v + inst * 512), 16, off, 0, 0, kDmaPolicy);
-        }
-      } else {
-#pragma unroll
-        for (int t = 0; t < NI; ++t) {
-          const int inst = inst_of(t);
-          const uint32_t off = of.o[t];
-          if (t < INST_PER_WAVE)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(kcR, FL_LDS(sl.k + inst * 512), 16, off, 0, 0, kDmaPolicy);
-          else
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(vcR, FL_LDS(sl.v + inst * 512), 16, off, 0, 0, kDmaPolicy);
-        }
+      for (int t = 0; t < NI; ++t) {
+        const uint32_t off = of.o[t];
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(srcN, FL_LDS(dst + inst_of(t) * 512), 16, off, 0, 0, kDmaPolicy);
       }
     } else {
-      uint16_t* dst = v_wave ? sl.v : sl.k;
-      if (u >= n_old) {                   // uniform: one of two scalar branches, same op count
 #pragma unroll
-        for (int t = 0; t < NI; ++t) {
-          const uint32_t off = of.o[t];
-          __builtin_amdgcn_raw_ptr_buffer_load_lds(srcN, FL_LDS(dst + inst_of(t) * 512), 16, off, 0, 0, kDmaPolicy);
-        }
-      } else {
-#pragma unroll
-        for (int t = 0; t < NI; ++t) {
-          const uint32_t off = of.o[t];
-          __builtin_amdgcn_raw_ptr_buffer_load_lds(srcC, FL_LDS(dst + inst_of(t) * 512), 16, off, 0, 0, kDmaPolicy);
-        }
+      for (int t = 0; t < NI; ++t) {
+        const uint32_t off = of.o[t];
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(srcC, FL_LDS(dst + inst_of(t) * 512), 16, off, 0, 0, kDmaPolicy);
       }
     }
   };
@@ -321,13 +271,13 @@ __global__ __launch_bounds__(256, 2) void loop_attn_kernel(AttnArgs a) {
   // wave w converts, in place, the V rows its own LDS-DMA wrote (bf16 -> fp16, exact for |v| in
   // [2^-14, 65504]); the barrier that follows publishes them to the other waves
   auto convert_v = [=](Slot<D>& sl) {
+    if (!v_wave) return;
     u32x4 w[NI];
 #pragma unroll
     for (int t = 0; t < NI; ++t)           // all reads first: one LDS round trip for the batch
-      if (is_v_op(t)) w[t] = *reinterpret_cast<const u32x4*>(sl.v + inst_of(t) * 512 + lane * 8);
+      w[t] = *reinterpret_cast<const u32x4*>(sl.v + inst_of(t) * 512 + lane * 8);
 #pragma unroll
     for (int t = 0; t < NI; ++t) {
-      if (!is_v_op(t)) continue;
       u32x4 h;
 #pragma unroll
       for (int e = 0; e < 4; ++e)
@@ -381,11 +331,11 @@ __global__ __launch_bounds__(256, 2) void loop_attn_kernel(AttnArgs a) {
       full = clast <= gmin - a.window;
     } else {
       const int t_hi = clast != kPad ? clast : bandHi;
-      active = group_has_rows && c0 <= gmax && (DENSE || t_hi > gmin - a.window);
-      full = clast <= gmin && (DENSE || c0 > gmax - a.window);
+      active = group_has_rows && c0 <= gmax && t_hi > gmin - a.window;
+      full = clast <= gmin && c0 > gmax - a.window;
     }
     if (!active) return;
-    if (!DENSE && add_pass && !newer && th.any) full = false;   // updated columns drop out
+    if (add_pass && !newer && th.any) full = false;   // updated columns drop out
     // S^T = K Q^T: lane holds columns 8j + 4hw + i of row r32
     f32x16 s = f32x16{};
 #pragma unroll
@@ -396,9 +346,9 @@ __global__ __launch_bounds__(256, 2) void loop_attn_kernel(AttnArgs a) {
     // masks, softmax and O^T += V^T P^T over the lane's 16 elements, fp16 operands
     constexpr int NE = 16;
     if (!full) {
-      // column masks: list columns need j + window <= i, band columns i - window < j <= i (any j <= i in
-      // the dense loop); padding and, for the add pass, the columns updated this loop carry kPad
-      const int view = (!DENSE && add_pass) ? 1 : 0;
+      // column masks: list columns need j + window <= i, band columns i - window < j <= i; padding and, for the
+      // add pass, the columns updated this loop carry kPad
+      const int view = add_pass ? 1 : 0;
       int cc[16];
 #pragma unroll
       for (int j = 0; j < NE / 4; ++j) {
@@ -409,9 +359,6 @@ __global__ __launch_bounds__(256, 2) void loop_attn_kernel(AttnArgs a) {
         const int lim = row_i - a.window;
 #pragma unroll
         for (int v = 0; v < NE; ++v) s[v] = cc[v] <= lim ? s[v] : -INFINITY;
-      } else if (DENSE) {
-#pragma unroll
-        for (int v = 0; v < NE; ++v) s[v] = cc[v] <= row_i ? s[v] : -INFINITY;
       } else {
         const uint32_t w = (uint32_t)a.window;
 #pragma unroll
@@ -473,9 +420,9 @@ __global__ __launch_bounds__(256, 2) void loop_attn_kernel(AttnArgs a) {
   // load in the sparse update and 2 * INST_PER_WAVE DMA), so "tile s has landed" is exactly
   // vmcnt(2 * OPS_PER_STEP) on every path.
   // Every wave loads the records (equal op counts keep every wait exact); one wave writes the tables:
-  // an add wave when the subtract waves convert all of V.
-  const bool rec_wave = __builtin_amdgcn_readfirstlane(wave) == (SPLIT_KV ? 2 : 0);
-  constexpr int OPS_PER_STEP = (DENSE ? 0 : 1) + NI;
+  // an add wave, as the subtract waves convert all of V.
+  const bool rec_wave = __builtin_amdgcn_readfirstlane(wave) == 2;
+  constexpr int OPS_PER_STEP = 1 + NI;
   // Records are loaded four steps before they are turned into tables (step s loads tile s + 8 and
   // describes tile s + 4), so the wave that writes the tables never waits for them: a record load is
   // always older than the tile load the step waits for.
@@ -530,71 +477,54 @@ __global__ __launch_bounds__(256, 2) void loop_attn_kernel(AttnArgs a) {
   // hand-off through the idle ring: group g uses slot g (D * 128 bytes >= 32 rows x D floats); the
   // subtract waves hand their term and mass to the add waves of the same rows
   float4* xacc = reinterpret_cast<float4*>(group == 0 ? &s0 : &s1);
-  if constexpr (!DENSE) {
-    if (!add_pass) {
+  if (!add_pass) {
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        xacc[(db * 4 + j) * 64 + lane] =
+            make_float4(acc[db][4 * j], acc[db][4 * j + 1], acc[db][4 * j + 2], acc[db][4 * j + 3]);
+    xm[group][lane] = msub;
+  }
+  lds_barrier();
+  if (!add_pass) return;
+  msub = xm[group][lane];
+  if (!row_ok) return;
+  const int64_t orow = ((int64_t)b * a.N + row_i) * HD + (int64_t)h * D;
+  const int64_t lrow = ((int64_t)b * a.N + row_i) * a.H + h;
+  const int64_t trow = ((int64_t)b * a.k + p) * a.H + h;
+  const bool keep = a.term_out != nullptr;
+  if (!(msub > 0.0f) || !(lsum > 0.0f)) {     // empty column set or vanished mass: unchanged
+    if (keep) {
 #pragma unroll
       for (int db = 0; db < DB; ++db)
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-          xacc[(db * 4 + j) * 64 + lane] =
-              make_float4(acc[db][4 * j], acc[db][4 * j + 1], acc[db][4 * j + 2], acc[db][4 * j + 3]);
-      xm[group][lane] = msub;
+          *reinterpret_cast<float4*>(a.term_out + trow * D + db * 32 + 8 * j + 4 * hw) = make_float4(0, 0, 0, 0);
+      if (hw == 0) a.mass_out[trow] = 0.0f;
     }
-    lds_barrier();
-    if (!add_pass) return;
-    msub = xm[group][lane];
+    return;
   }
-  if (!row_ok) return;
-  const int64_t orow = ((int64_t)b * a.N + row_i) * HD + (int64_t)h * D;
-  const int64_t lrow = ((int64_t)b * a.N + row_i) * a.H + h;
-  if constexpr (DENSE) {
-    if (!(lsum > 0.0f)) return;    // unreachable: column 0 is always causal
-    const float inv = 1.0f / lsum;
+  const float f = msub / lsum;
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
+  for (int db = 0; db < DB; ++db)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int dim = db * 32 + 8 * j + 4 * hw;
-        float4 out = make_float4(acc[db][4 * j] * inv, acc[db][4 * j + 1] * inv,
-                                 acc[db][4 * j + 2] * inv, acc[db][4 * j + 3] * inv);
-        *reinterpret_cast<float4*>(a.o + orow + dim) = out;
-      }
-    if (hw == 0) a.lse_ref[lrow] = (run_max + log2f(lsum)) * 0.6931471805599453f;
-  } else {
-    const int64_t trow = ((int64_t)b * a.k + p) * a.H + h;
-    const bool keep = a.term_out != nullptr;
-    if (!(msub > 0.0f) || !(lsum > 0.0f)) {     // empty column set or vanished mass: unchanged
-      if (keep) {
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            *reinterpret_cast<float4*>(a.term_out + trow * D + db * 32 + 8 * j + 4 * hw) = make_float4(0, 0, 0, 0);
-        if (hw == 0) a.mass_out[trow] = 0.0f;
-      }
-      return;
+    for (int j = 0; j < 4; ++j) {
+      const int dim = db * 32 + 8 * j + 4 * hw;
+      const float4 sub = xacc[(db * 4 + j) * 64 + lane];
+      const float4 add = make_float4(acc[db][4 * j + 0] * f, acc[db][4 * j + 1] * f,
+                                     acc[db][4 * j + 2] * f, acc[db][4 * j + 3] * f);
+      float4 prev = *reinterpret_cast<const float4*>(a.o + orow + dim);
+      prev.x = prev.x - sub.x + add.x;
+      prev.y = prev.y - sub.y + add.y;
+      prev.z = prev.z - sub.z + add.z;
+      prev.w = prev.w - sub.w + add.w;
+      *reinterpret_cast<float4*>(a.o + orow + dim) = prev;
+      if (keep) *reinterpret_cast<float4*>(a.term_out + trow * D + dim) = add;
     }
-    const float f = msub / lsum;
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int dim = db * 32 + 8 * j + 4 * hw;
-        const float4 sub = xacc[(db * 4 + j) * 64 + lane];
-        const float4 add = make_float4(acc[db][4 * j + 0] * f, acc[db][4 * j + 1] * f,
-                                       acc[db][4 * j + 2] * f, acc[db][4 * j + 3] * f);
-        float4 prev = *reinterpret_cast<const float4*>(a.o + orow + dim);
-        prev.x = prev.x - sub.x + add.x;
-        prev.y = prev.y - sub.y + add.y;
-        prev.z = prev.z - sub.z + add.z;
-        prev.w = prev.w - sub.w + add.w;
-        *reinterpret_cast<float4*>(a.o + orow + dim) = prev;
-        if (keep) *reinterpret_cast<float4*>(a.term_out + trow * D + dim) = add;
-      }
-    if (hw == 0) {
-      a.lse_ref[lrow] = (run_max + log2f(lsum)) * 0.6931471805599453f - logf(msub);
-      if (keep) a.mass_out[trow] = msub;
-    }
+  if (hw == 0) {
+    a.lse_ref[lrow] = (run_max + log2f(lsum)) * 0.6931471805599453f - logf(msub);
+    if (keep) a.mass_out[trow] = msub;
   }
 }
 
@@ -1614,16 +1544,11 @@ static int loop_sparse_attn(const uint16_t* q_cur, const uint16_t* q_prev, const
     int rc = check_launch("attn_prep_kernel");
     if (rc != FL_OK) return rc;
   }
-  const int bm = dense ? 128 : 64;          // rows per workgroup
-  dim3 grid(((k + bm - 1) / bm) * B * H);
-  if (dense) {
-    if (d == 128) loop_attn_kernel<128, kDense><<<grid, 256, 0, st>>>(a);
-    else loop_attn_kernel<64, kDense><<<grid, 256, 0, st>>>(a);
-    return check_launch("loop_attn_kernel");
-  }
+  if (dense) return launch_dense(q_cur, k_cache, v_cache, B, N, H, d, sm_scale, lse_ref, o, st);
+  dim3 grid(((k + 63) / 64) * B * H);       // 64 rows per workgroup
   if (!reuse) {
-    if (d == 128) loop_attn_kernel<128, kFull><<<grid, 256, 0, st>>>(a);
-    else loop_attn_kernel<64, kFull><<<grid, 256, 0, st>>>(a);
+    if (d == 128) loop_attn_kernel<128><<<grid, 256, 0, st>>>(a);
+    else loop_attn_kernel<64><<<grid, 256, 0, st>>>(a);
     return check_launch("loop_attn_kernel");
   }
 #define FL_REUSE(DD, CC) reuse_attn_kernel<DD, CC><<<grid, 256, 0, st>>>(a)

@@ -98,6 +98,10 @@ __device__ __forceinline__ float row4_add(float x) { return xor32_add(xor16_add(
 // argument, so the median is not folded back into a maximum with its NaN-quieting steps
 __device__ __forceinline__ float fmax_nn(float x, float y, float pinf) { return __builtin_amdgcn_fmed3f(x, y, pinf); }
 
+// The dense source loop (fl_dense_attn.hip): every row over all causal columns.
+int launch_dense(const uint16_t* q, const uint16_t* k, const uint16_t* v, int B, int N, int H, int d, float sm_scale,
+                 float* lse, float* o, hipStream_t st);
+
 // Whether the segment kernels (fl_seg_attn.hip) cover a shape.
 bool seg_supported(int k, int c_list, int window, int N, int d);
 
