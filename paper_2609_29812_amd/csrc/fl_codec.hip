@@ -9,7 +9,11 @@
 //                 with lane shuffles.
 //   dequant       rebuilds bf16(x_hat + z + q*s) rows, compact or in place.
 // Both quantizers optionally write the reconstructed rows (fusing the compact dequantization).
-#include "fl_common.h"
+//
+// The quantizers are bound by vector instructions as much as by HBM (a 32K base of 16 heads x 128 in 4 bits moves
+// 620 MB, 118 us at the rate of a large copy): per value about 50 instructions, of which a third for the group's
+// metadata in fp64 and a 64-bit division for the row, took 158 us; 31 a value, the count now, take 130 us.
+#include "fl_attn_util.h"
 
 namespace fl {
 
@@ -29,20 +33,10 @@ __device__ __forceinline__ Row8 load_bf16x8(const uint16_t* p) {
   return r;
 }
 
-__device__ __forceinline__ void store_bf16x8(uint16_t* p, const Row8& r) {
-  uint32_t ws[4];
-#pragma unroll
-  for (int t = 0; t < 4; ++t)
-    ws[t] = f32_to_bf16_rne(r.v[2 * t]) | (f32_to_bf16_rne(r.v[2 * t + 1]) << 16);
-  *reinterpret_cast<uint4*>(p) = make_uint4(ws[0], ws[1], ws[2], ws[3]);
-}
-
-// Two fp32 values to packed fp16 (round to nearest even; v_cvt_pk_f16_f32, the conversion the attention
-// kernels apply to bf16 value rows in LDS).
-__device__ __forceinline__ uint32_t f16x2_bits(float a, float b) {
-  typedef float f2 __attribute__((ext_vector_type(2)));
-  typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2){a, b}, h2));
+// Eight values rounded to bf16 (to nearest even, v_cvt_pk_bf16_f32), packed.
+__device__ __forceinline__ uint4 to_bf16x8(const Row8& r) {
+  return make_uint4(pack_bf16x2(r.v[0], r.v[1]), pack_bf16x2(r.v[2], r.v[3]), pack_bf16x2(r.v[4], r.v[5]),
+                    pack_bf16x2(r.v[6], r.v[7]));
 }
 
 // Eight bf16 values (as packed bits) to fp16.
@@ -50,22 +44,12 @@ __device__ __forceinline__ uint4 bf16x8_to_f16(uint4 w) {
   const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
   uint32_t o[4];
 #pragma unroll
-  for (int t = 0; t < 4; ++t) o[t] = f16x2_bits(__uint_as_float(ws[t] << 16), __uint_as_float(ws[t] & 0xFFFF0000u));
+  for (int t = 0; t < 4; ++t) o[t] = pack_f16x2(__uint_as_float(ws[t] << 16), __uint_as_float(ws[t] & 0xFFFF0000u));
   return make_uint4(o[0], o[1], o[2], o[3]);
 }
 
-// The fp16 copy of a row chunk as store_bf16x8 writes it: each value rounded to bf16 first, then to fp16.
-__device__ __forceinline__ void store_f16x8_of_bf16(uint16_t* p, const Row8& r) {
-  uint32_t o[4];
-#pragma unroll
-  for (int t = 0; t < 4; ++t)
-    o[t] = f16x2_bits(__uint_as_float(f32_to_bf16_rne(r.v[2 * t]) << 16),
-                      __uint_as_float(f32_to_bf16_rne(r.v[2 * t + 1]) << 16));
-  *reinterpret_cast<uint4*>(p) = make_uint4(o[0], o[1], o[2], o[3]);
-}
-
-// Reciprocal of a metadata scale for encode1 (within 1 ulp; s is an fp16 value, so 1/s is a normal fp32).
-__device__ __forceinline__ float scale_rcp(float s) { return __builtin_amdgcn_rcpf(s); }
+// Reciprocal of a metadata scale for encode1 (within 1 ulp; s is an fp16 value, so 1/s is a normal fp32), 0 for s = 0.
+__device__ __forceinline__ float scale_rcp(float s) { return s == 0.0f ? 0.0f : __builtin_amdgcn_rcpf(s); }
 
 // Encode one value: q = clamp(rint(fp32(fp32(delta - z) / s)), 0, qmax), 0 when s == 0, with rs = scale_rcp(s).
 // No division: q1 = a rs, e = a - q1 s (one fma, exact), q2 = e rs + q1 (one fma) is Markstein's correction
@@ -74,14 +58,13 @@ __device__ __forceinline__ float scale_rcp(float s) { return __builtin_amdgcn_rc
 // two that keeps a/s either exactly at a half-integer m + 1/2 or more than half an ulp away from it (by
 // 2^-11 of that half ulp at least): rint(q2) is rint of the correctly rounded quotient, the IEEE division's
 // code, bit for bit (checked in exact arithmetic on the host, ties and fp32 neighbours of every boundary).
-__device__ __forceinline__ uint32_t encode1(float delta, float z, float s, float rs, int qmax) {
+// Returned as a float.
+__device__ __forceinline__ float encode1(float delta, float z, float s, float rs, int qmax) {
   const float a = delta - z;
   const float q1 = a * rs;
   const float e = __builtin_fmaf(-q1, s, a);
-  float t = __builtin_fmaf(e, rs, q1);
-  t = __builtin_rintf(t);
-  t = fminf(fmaxf(t, 0.0f), (float)qmax);
-  return s == 0.0f ? 0u : (uint32_t)t;
+  // (a median with 0 and qmax: the clamp in one step, 0 for NaN)
+  return __builtin_amdgcn_fmed3f(__builtin_rintf(__builtin_fmaf(e, rs, q1)), 0.0f, (float)qmax);
 }
 
 template <int BITS>
@@ -117,11 +100,59 @@ __device__ __forceinline__ void load_codes8(const uint8_t* src, uint32_t q[8]) {
   }
 }
 
-// Group metadata from fp32 min/max: z = fp16 down(min), s = fp16 up((max - z) / qmax), both fp64.
-__device__ __forceinline__ void group_meta(float mn, float mx, int qmax, double& z, double& s) {
-  z = f16_down_value((double)mn);
-  s = f16_up_value(((double)mx - z) / (double)qmax);
+// Group metadata from fp32 min/max: z = the largest fp16 <= min, s = the smallest fp16 >= fp64((max - z) / qmax), both
+// saturating at +-65504, zeros as +0.
+//
+// Without fp64: z is the fp16 towards zero, a step further down if that is above min.  With d = max - z exact in fp32
+// and not negative, s is the smallest fp16 with s qmax >= d (s qmax has at most 19 significant bits, exact in fp32, and
+// d 24, so d / qmax is s itself or further than an fp64 rounding from it): the fp16 towards zero of d / qmax by the
+// reciprocal (off by less than a step), moved up while s qmax < d.  Otherwise the fp64 form (a rare branch).
+struct GroupMeta {
+  float z, s;
+  uint32_t zb, sb;      // their fp16 bits
+};
+
+__device__ __forceinline__ uint32_t f16_towards_zero(float x) {
+  return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(x, 0.0f)) & 0xFFFFu;
 }
+
+template <int QMAX>
+__device__ __forceinline__ GroupMeta group_meta(float mn, float mx) {
+  GroupMeta m;
+  const float x = __builtin_amdgcn_fmed3f(mn, -65504.0f, 65504.0f);
+  m.zb = f16_towards_zero(x);
+  m.zb += f16_bits_to_f32(m.zb) > x ? 1u : 0u;             // (only below zero: a step away from it)
+  if (m.zb == 0x8000u) m.zb = 0u;
+  m.z = f16_bits_to_f32(m.zb);
+  const float d = mx - m.z;
+  const float bb = d - mx;                                 // TwoSum: the rounding error of d
+  const float err = (mx - (d - bb)) + (-m.z - bb);
+  constexpr float q = (float)QMAX, rq = 1.0f / q;
+  m.sb = f16_towards_zero(fminf(d * rq, 65504.0f));
+  m.sb += f16_bits_to_f32(m.sb) * q < d ? 1u : 0u;
+  m.sb += f16_bits_to_f32(m.sb) * q < d ? 1u : 0u;
+  m.sb = min(m.sb, 0x7BFFu);
+  if (!(err == 0.0f && d >= 0.0f)) {
+    const double zd = f16_down_value((double)mn);
+    const double sd = f16_up_value(((double)mx - zd) / (double)QMAX);
+    m.zb = f16_bits_of_exact(zd);
+    m.sb = f16_bits_of_exact(sd);
+    m.z = (float)zd;
+  }
+  m.s = f16_bits_to_f32(m.sb);
+  return m;
+}
+
+// min / max with a lane of the same 16-lane row (DPP, no LDS).  As medians with an infinity: a plain fminf adds a
+// NaN-quieting step per operand, and no NaN gets here (the running min and max start at the infinities and drop them).
+#define FL_DPP_F(x, ctrl) \
+  __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(x), __float_as_int(x), (ctrl), 0xf, 0xf, false))
+#define FL_DPP_MINMAX(mn, mx, ctrl, inf)                            \
+  do {                                                              \
+    mn = __builtin_amdgcn_fmed3f(mn, FL_DPP_F(mn, ctrl), -(inf));   \
+    mx = __builtin_amdgcn_fmed3f(mx, FL_DPP_F(mx, ctrl), (inf));    \
+  } while (0)
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kMirror8 = 0x141, kMirror16 = 0x140, kXor8 = 0x128;   // (xor 8: rotate by 8)
 
 // ---- keys: per-channel groups along packed rows ----------------------------------------------------
 // A workgroup of 256 threads = S row slices x CH chunks of 8 channels; each slice holds RPS = G/S rows.
@@ -135,12 +166,16 @@ __device__ __forceinline__ void quant_token_body(
     const uint16_t* __restrict__ x_cur, const uint16_t* x_ref,
     const int32_t* __restrict__ idx, int k, int N, int HD, int G, uint8_t* __restrict__ codes,
     uint16_t* __restrict__ scale, uint16_t* __restrict__ zero, uint16_t* out_rows, bool commit,
-    int bx, int g, int b) {
+    int bx, int g, int b, float pinf) {
   constexpr int CH = 256 / S;          // chunks of 8 channels per workgroup
-  __shared__ float s_mn[S][CH * 8];
-  __shared__ float s_mx[S][CH * 8];
+  // CH = 8: lanes l and l ^ 8 of a wave hold two slices of the same channels, joined in registers first
+  constexpr int JOIN = CH == 8 ? 2 : 1, P = S / JOIN;
+  constexpr int PARTS = CH == 8 ? 4 : 1;   // threads that reduce one channel
+  __shared__ float s_mn[P][CH * 8 + 16 * (PARTS > 1)];
+  __shared__ float s_mx[P][CH * 8 + 16 * (PARTS > 1)];
   __shared__ float s_z[CH * 8];
   __shared__ float s_s[CH * 8];
+  __shared__ float s_r[CH * 8];
   constexpr int qmax = (1 << BITS) - 1;
   const int slice = threadIdx.x / CH, chunk = threadIdx.x % CH;
   const int c0 = bx * (CH * 8) + chunk * 8;
@@ -153,53 +188,69 @@ __device__ __forceinline__ void quant_token_body(
   float mn[8], mx[8];
 #pragma unroll
   for (int t = 0; t < 8; ++t) { mn[t] = INFINITY; mx[t] = -INFINITY; }
+  // (past the group's last row that row again, past the last channel the last ones: neither moves a minimum or
+  // maximum that is used, and nothing branches)
+  const int cl = min(c0, HD - 8);
 #pragma unroll
   for (int j = 0; j < RPS; ++j) {
-    const int p = g * G + slice * RPS + j;
+    const int p = min(g * G + slice * RPS + j, k - 1);
+    const int64_t i = idx ? (int64_t)idx[(int64_t)b * k + p] : (int64_t)p;
+    const int64_t off = ((int64_t)b * N + i) * HD + cl;
+    roff[j] = off;
+    const Row8 c = load_bf16x8(x_cur + off);
+    Row8 r{};
     ref_raw[j] = make_uint4(0, 0, 0, 0);
-    roff[j] = 0;
-    if (ch_ok && p < k) {
-      const int64_t i = idx ? (int64_t)idx[(int64_t)b * k + p] : (int64_t)p;
-      const int64_t off = ((int64_t)b * N + i) * HD + c0;
-      roff[j] = off;
-      Row8 c = load_bf16x8(x_cur + off);
-      Row8 r{};
-      if (x_ref) {
-        ref_raw[j] = *reinterpret_cast<const uint4*>(x_ref + off);
-        r = load_bf16x8(x_ref + off);
-      }
+    if (x_ref) {
+      ref_raw[j] = *reinterpret_cast<const uint4*>(x_ref + off);
+      r = load_bf16x8(x_ref + off);
+    }
 #pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        dl[j][t] = c.v[t] - r.v[t];
-        mn[t] = fminf(mn[t], dl[j][t]);
-        mx[t] = fmaxf(mx[t], dl[j][t]);
-      }
+    for (int t = 0; t < 8; ++t) dl[j][t] = c.v[t] - r.v[t];
+  }
+#pragma unroll
+  for (int j = 0; j < RPS; ++j)
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      mn[t] = fminf(mn[t], dl[j][t]);
+      mx[t] = fmaxf(mx[t], dl[j][t]);
+    }
+  if constexpr (JOIN == 2) {
+#pragma unroll
+    for (int t = 0; t < 8; ++t) FL_DPP_MINMAX(mn[t], mx[t], kXor8, pinf);
+  }
+  if (JOIN == 1 || (slice & 1) == 0) {
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      s_mn[slice / JOIN][chunk * 8 + t] = mn[t];
+      s_mx[slice / JOIN][chunk * 8 + t] = mx[t];
     }
   }
-#pragma unroll
-  for (int t = 0; t < 8; ++t) {
-    s_mn[slice][chunk * 8 + t] = mn[t];
-    s_mx[slice][chunk * 8 + t] = mx[t];
-  }
   __syncthreads();
-  if (threadIdx.x < CH * 8) {
-    const int ch = threadIdx.x;   // one thread per channel
+  if (threadIdx.x < CH * 8 * PARTS) {
+    const int ch = threadIdx.x / PARTS, part = threadIdx.x % PARTS;   // PARTS adjacent threads per channel
     const int c = bx * (CH * 8) + ch;
     float a = INFINITY, bb = -INFINITY;
 #pragma unroll
-    for (int sl = 0; sl < S; ++sl) {
-      a = fminf(a, s_mn[sl][ch]);
-      bb = fmaxf(bb, s_mx[sl][ch]);
+    for (int sl = 0; sl < P / PARTS; ++sl) {
+      a = fminf(a, s_mn[sl * PARTS + part][ch]);
+      bb = fmaxf(bb, s_mx[sl * PARTS + part][ch]);
     }
-    double z = 0.0, s = 0.0;
-    if (c < HD) {
-      group_meta(a, bb, qmax, z, s);
+    if constexpr (PARTS == 4) {
+      FL_DPP_MINMAX(a, bb, kXor1, pinf);
+      FL_DPP_MINMAX(a, bb, kXor2, pinf);
+    }
+    GroupMeta gm = {};
+    if (c < HD) gm = group_meta<qmax>(a, bb);
+    if (c < HD && part == 0) {
       const int64_t m = ((int64_t)b * ng + g) * HD + c;
-      zero[m] = (uint16_t)f16_bits_of_exact(z);
-      scale[m] = (uint16_t)f16_bits_of_exact(s);
+      zero[m] = (uint16_t)gm.zb;
+      scale[m] = (uint16_t)gm.sb;
     }
-    s_z[ch] = (float)z;
-    s_s[ch] = (float)s;
+    if (part == 0) {
+      s_z[ch] = gm.z;
+      s_s[ch] = gm.s;
+      s_r[ch] = scale_rcp(gm.s);
+    }
   }
   __syncthreads();
   if (!ch_ok) return;
@@ -208,16 +259,20 @@ __device__ __forceinline__ void quant_token_body(
   for (int t = 0; t < 8; ++t) {
     z8[t] = s_z[chunk * 8 + t];
     s8[t] = s_s[chunk * 8 + t];
-    r8[t] = scale_rcp(s8[t]);
+    r8[t] = s_r[chunk * 8 + t];
   }
   const int row_bytes = HD * BITS / 8;
 #pragma unroll
   for (int j = 0; j < RPS; ++j) {
     const int p = g * G + slice * RPS + j;
     if (p >= k) break;
+    float f[8];
     uint32_t q[8];
 #pragma unroll
-    for (int t = 0; t < 8; ++t) q[t] = encode1(dl[j][t], z8[t], s8[t], r8[t], qmax);
+    for (int t = 0; t < 8; ++t) {
+      f[t] = encode1(dl[j][t], z8[t], s8[t], r8[t], qmax);
+      q[t] = (uint32_t)f[t];
+    }
     store_codes8<BITS>(codes + ((int64_t)b * k + p) * row_bytes + c0 * BITS / 8, q);
     if (out_rows) {
       const uint32_t rw[4] = {ref_raw[j].x, ref_raw[j].y, ref_raw[j].z, ref_raw[j].w};
@@ -225,10 +280,9 @@ __device__ __forceinline__ void quant_token_body(
 #pragma unroll
       for (int t = 0; t < 8; ++t) {
         float ref = (t & 1) ? __uint_as_float(rw[t >> 1] & 0xFFFF0000u) : __uint_as_float(rw[t >> 1] << 16);
-        float dq = z8[t] + (float)q[t] * s8[t];     // q * s exact in fp32: one rounding
-        o.v[t] = ref + dq;
+        o.v[t] = ref + __builtin_fmaf(f[t], s8[t], z8[t]);     // q * s is exact in fp32: one rounding
       }
-      store_bf16x8(out_rows + (commit ? roff[j] : ((int64_t)b * k + p) * HD + c0), o);
+      *reinterpret_cast<uint4*>(out_rows + (commit ? roff[j] : ((int64_t)b * k + p) * HD + c0)) = to_bf16x8(o);
     }
   }
 }
@@ -237,9 +291,9 @@ template <int BITS, int S, int RPS>
 __global__ __launch_bounds__(256) void quant_token_kernel(
     const uint16_t* __restrict__ x_cur, const uint16_t* x_ref,
     const int32_t* __restrict__ idx, int k, int N, int HD, int G, uint8_t* __restrict__ codes,
-    uint16_t* __restrict__ scale, uint16_t* __restrict__ zero, uint16_t* out_rows, bool commit) {
+    uint16_t* __restrict__ scale, uint16_t* __restrict__ zero, uint16_t* out_rows, bool commit, float pinf) {
   quant_token_body<BITS, S, RPS>(x_cur, x_ref, idx, k, N, HD, G, codes, scale, zero, out_rows, commit,
-                                 blockIdx.x, blockIdx.y, blockIdx.z);
+                                 blockIdx.x, blockIdx.y, blockIdx.z, pinf);
 }
 
 // ---- values: per-token groups of G channels ----------------------------------------------------------
@@ -250,12 +304,12 @@ __device__ __forceinline__ void quant_channel_body(
     const uint16_t* __restrict__ x_cur, const uint16_t* x_ref,
     const int32_t* __restrict__ idx, int k, int N, int HD, int G, uint8_t* __restrict__ codes,
     uint16_t* __restrict__ scale, uint16_t* __restrict__ zero, uint16_t* out_rows, bool commit,
-    int64_t local, int b, uint16_t* out_f16 = nullptr) {
+    int64_t local, int b, float pinf, uint16_t* out_f16 = nullptr) {
   constexpr int qmax = (1 << BITS) - 1;
   const int chunks = HD / 8;
-  const bool ok = local < (int64_t)k * chunks;
-  const int p = ok ? (int)(local / chunks) : 0;
-  const int chunk = ok ? (int)(local % chunks) : 0;
+  const bool ok = local < (int64_t)k * chunks;         // (k HD < 2^31: 32-bit quotients)
+  const int p = ok ? (int)((uint32_t)local / (uint32_t)chunks) : 0;
+  const int chunk = ok ? (int)local - p * chunks : 0;
   const int c0 = chunk * 8;
   float dl[8];
   uint4 ref_raw = make_uint4(0, 0, 0, 0);
@@ -279,22 +333,26 @@ __device__ __forceinline__ void quant_channel_body(
     }
   }
   // reduce across the G/8 consecutive lanes of the group (groups never straddle a wave)
-  for (int off = 1; off < G / 8; off <<= 1) {
-    mn = fminf(mn, __shfl_xor(mn, off, 64));
-    mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-  }
+  if (G > 8) FL_DPP_MINMAX(mn, mx, kXor1, pinf);
+  if (G > 16) FL_DPP_MINMAX(mn, mx, kXor2, pinf);
+  if (G > 32) FL_DPP_MINMAX(mn, mx, kMirror8, pinf);         // (quads are uniform by now)
+  if (G > 64) FL_DPP_MINMAX(mn, mx, kMirror16, pinf);
   if (!ok) return;
-  double z, s;
-  group_meta(mn, mx, qmax, z, s);
-  if ((chunk % (G / 8)) == 0) {
-    const int64_t m = ((int64_t)b * k + p) * (HD / G) + c0 / G;
-    zero[m] = (uint16_t)f16_bits_of_exact(z);
-    scale[m] = (uint16_t)f16_bits_of_exact(s);
+  const GroupMeta gm = group_meta<qmax>(mn, mx);
+  const int lg = __builtin_ctz(G);                       // (G is a power of two)
+  if ((c0 & (G - 1)) == 0) {
+    const int64_t m = ((int64_t)b * k + p) * (HD >> lg) + (c0 >> lg);
+    zero[m] = (uint16_t)gm.zb;
+    scale[m] = (uint16_t)gm.sb;
   }
-  const float z32 = (float)z, s32 = (float)s, r32 = scale_rcp(s32);
+  const float z32 = gm.z, s32 = gm.s, r32 = scale_rcp(s32);
+  float f[8];
   uint32_t q[8];
 #pragma unroll
-  for (int t = 0; t < 8; ++t) q[t] = encode1(dl[t], z32, s32, r32, qmax);
+  for (int t = 0; t < 8; ++t) {
+    f[t] = encode1(dl[t], z32, s32, r32, qmax);
+    q[t] = (uint32_t)f[t];
+  }
   store_codes8<BITS>(codes + ((int64_t)b * k + p) * (HD * BITS / 8) + c0 * BITS / 8, q);
   if (out_rows) {
     const uint32_t rw[4] = {ref_raw.x, ref_raw.y, ref_raw.z, ref_raw.w};
@@ -302,10 +360,11 @@ __device__ __forceinline__ void quant_channel_body(
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
       float ref = (t & 1) ? __uint_as_float(rw[t >> 1] & 0xFFFF0000u) : __uint_as_float(rw[t >> 1] << 16);
-      o.v[t] = ref + (z32 + (float)q[t] * s32);
+      o.v[t] = ref + __builtin_fmaf(f[t], s32, z32);
     }
-    store_bf16x8(out_rows + (commit ? roff : ((int64_t)b * k + p) * HD + c0), o);
-    if (out_f16) store_f16x8_of_bf16(out_f16 + roff, o);   // (commit only: the cache row's fp16 copy)
+    const uint4 w = to_bf16x8(o);
+    *reinterpret_cast<uint4*>(out_rows + (commit ? roff : ((int64_t)b * k + p) * HD + c0)) = w;
+    if (out_f16) *reinterpret_cast<uint4*>(out_f16 + roff) = bf16x8_to_f16(w);   // (commit only: the cache row's copy)
   }
 }
 
@@ -313,9 +372,9 @@ template <int BITS>
 __global__ __launch_bounds__(256) void quant_channel_kernel(
     const uint16_t* __restrict__ x_cur, const uint16_t* x_ref,
     const int32_t* __restrict__ idx, int k, int N, int HD, int G, uint8_t* __restrict__ codes,
-    uint16_t* __restrict__ scale, uint16_t* __restrict__ zero, uint16_t* out_rows, bool commit) {
+    uint16_t* __restrict__ scale, uint16_t* __restrict__ zero, uint16_t* out_rows, bool commit, float pinf) {
   quant_channel_body<BITS>(x_cur, x_ref, idx, k, N, HD, G, codes, scale, zero, out_rows, commit,
-                           (int64_t)blockIdx.x * blockDim.x + threadIdx.x, blockIdx.y);
+                           (int64_t)blockIdx.x * blockDim.x + threadIdx.x, blockIdx.y, pinf);
 }
 
 // ---- keys and values in one launch -------------------------------------------------------------------
@@ -339,6 +398,7 @@ struct QuantKV {
   int k, N, HD, G;
   int kx, ky, vx;      // key workgroups per (row group, batch) and row groups; value workgroups per batch
   int commit;
+  float pinf;          // +inf (an argument, so that medians with it stay medians)
 };
 
 template <int BITS, int S, int RPS>
@@ -349,10 +409,10 @@ __global__ __launch_bounds__(256) void quant_kv_kernel(QuantKV a) {
   const int r = blk - b * (nkb + a.vx);
   if (r < nkb) {
     quant_token_body<BITS, S, RPS>(a.k_cur, a.k_ref, a.idx, a.k, a.N, a.HD, a.G, a.k_codes, a.k_scale,
-                                   a.k_zero, a.k_rows, a.commit != 0, r % a.kx, r / a.kx, b);
+                                   a.k_zero, a.k_rows, a.commit != 0, r % a.kx, r / a.kx, b, a.pinf);
   } else {
     quant_channel_body<BITS>(a.v_cur, a.v_ref, a.idx, a.k, a.N, a.HD, a.G, a.v_codes, a.v_scale, a.v_zero,
-                             a.v_rows, a.commit != 0, (int64_t)(r - nkb) * 256 + threadIdx.x, b, a.v_f16);
+                             a.v_rows, a.commit != 0, (int64_t)(r - nkb) * 256 + threadIdx.x, b, a.pinf, a.v_f16);
   }
 }
 
@@ -365,7 +425,7 @@ __global__ __launch_bounds__(256) void passthrough_kernel(const uint16_t* __rest
   const int64_t local = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int b = blockIdx.y;
   if (local >= (int64_t)k * chunks) return;
-  const int p = (int)(local / chunks), c0 = (int)(local % chunks) * 8;
+  const int p = (int)((uint32_t)local / (uint32_t)chunks), c0 = ((int)local - p * chunks) * 8;
   const int64_t i = idx ? (int64_t)idx[(int64_t)b * k + p] : (int64_t)p;
   uint4 w = *reinterpret_cast<const uint4*>(x_cur + ((int64_t)b * N + i) * HD + c0);
   *reinterpret_cast<uint4*>(codes + (((int64_t)b * k + p) * HD + c0) * 2) = w;
@@ -382,7 +442,7 @@ __device__ __forceinline__ void dequant_body(
     uint16_t* x_hat, uint16_t* out_rows, int64_t local, int b) {
   const int chunks = HD / 8;
   if (local >= (int64_t)k * chunks) return;
-  const int p = (int)(local / chunks), c0 = (int)(local % chunks) * 8;
+  const int p = (int)((uint32_t)local / (uint32_t)chunks), c0 = ((int)local - p * chunks) * 8;
   const int64_t i = idx ? (int64_t)idx[(int64_t)b * k + p] : (int64_t)p;
   const int64_t xoff = ((int64_t)b * N + i) * HD + c0;
   uint16_t* dst = out_rows ? out_rows + ((int64_t)b * k + p) * HD + c0 : x_hat + xoff;
@@ -414,7 +474,7 @@ __device__ __forceinline__ void dequant_body(
     Row8 o;
 #pragma unroll
     for (int t = 0; t < 8; ++t) o.v[t] = x.v[t] + (z8[t] + (float)q[t] * s8[t]);
-    store_bf16x8(dst, o);
+    *reinterpret_cast<uint4*>(dst) = to_bf16x8(o);
   }
 }
 
@@ -496,7 +556,7 @@ static int residual_quant(const char* fn, const uint16_t* x_cur, const uint16_t*
     dim3 grid((HD + cw - 1) / cw, (k + group - 1) / group, B);
 #define FL_QT(BB, SS, RR)                                                                          \
   quant_token_kernel<BB, SS, RR><<<grid, 256, 0, st>>>(x_cur, x_ref, idx, k, N, HD, group, codes, \
-                                                       scale, zero, out_rows, commit)
+                                                       scale, zero, out_rows, commit, INFINITY)
 #define FL_QT_BITS(BB)                                   \
   switch (group) {                                       \
     case 8: FL_QT(BB, 8, 1); break;                      \
@@ -512,7 +572,7 @@ static int residual_quant(const char* fn, const uint16_t* x_cur, const uint16_t*
   }
   dim3 grid((unsigned)(((int64_t)k * (HD / 8) + 255) / 256), B);
 #define FL_QC(BB) \
-  quant_channel_kernel<BB><<<grid, 256, 0, st>>>(x_cur, x_ref, idx, k, N, HD, group, codes, scale, zero, out_rows, commit)
+  quant_channel_kernel<BB><<<grid, 256, 0, st>>>(x_cur, x_ref, idx, k, N, HD, group, codes, scale, zero, out_rows, commit, INFINITY)
   if (bits == 2) FL_QC(2);
   else if (bits == 4) FL_QC(4);
   else FL_QC(8);
@@ -580,6 +640,7 @@ static int residual_quant_kv(const char* fn, const uint16_t* k_cur, uint16_t* k_
   a.ky = (k + group - 1) / group;
   a.vx = (int)(((int64_t)k * (HD / 8) + 255) / 256);
   a.commit = commit ? 1 : 0;
+  a.pinf = INFINITY;
   const int64_t blocks = ((int64_t)a.kx * a.ky + a.vx) * B;
   FL_REQUIRE(blocks < ((int64_t)1 << 31), FL_E_SHAPE, "%s: grid too large", fn);
   hipStream_t st = as_stream(stream);
