@@ -21,8 +21,13 @@ struct Row8 {
   float v[8];
 };
 
+// NT: marked non-temporal, for the new state, which is read once (a 32K base 134 -> 130 us)
+template <bool NT = false>
 __device__ __forceinline__ Row8 load_bf16x8(const uint16_t* p) {
-  uint4 w = *reinterpret_cast<const uint4*>(p);
+  u32x4 w0;
+  if constexpr (NT) w0 = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+  else w0 = *reinterpret_cast<const u32x4*>(p);
+  const uint4 w = make_uint4(w0[0], w0[1], w0[2], w0[3]);
   const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
   Row8 r;
 #pragma unroll
@@ -197,7 +202,7 @@ __device__ __forceinline__ void quant_token_body(
     const int64_t i = idx ? (int64_t)idx[(int64_t)b * k + p] : (int64_t)p;
     const int64_t off = ((int64_t)b * N + i) * HD + cl;
     roff[j] = off;
-    const Row8 c = load_bf16x8(x_cur + off);
+    const Row8 c = load_bf16x8<true>(x_cur + off);
     Row8 r{};
     ref_raw[j] = make_uint4(0, 0, 0, 0);
     if (x_ref) {
@@ -319,7 +324,7 @@ __device__ __forceinline__ void quant_channel_body(
     const int64_t i = idx ? (int64_t)idx[(int64_t)b * k + p] : (int64_t)p;
     const int64_t off = ((int64_t)b * N + i) * HD + c0;
     roff = off;
-    Row8 c = load_bf16x8(x_cur + off);
+    Row8 c = load_bf16x8<true>(x_cur + off);
     Row8 r{};
     if (x_ref) {
       ref_raw = *reinterpret_cast<const uint4*>(x_ref + off);
