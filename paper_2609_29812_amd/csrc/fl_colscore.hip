@@ -258,7 +258,7 @@ __global__ __launch_bounds__(256, NB == 1 ? 3 : 2) void colscore_kernel(CsArgs a
     seg = id % a.n_seg;
     rank = id / a.n_seg;
   }
-  const int wg = ROWS ? n_wg - 1 - rank : rank;
+  const int wg = ROWS && NB == 1 ? n_wg - 1 - rank : rank;
   const int gs = a.seg0 + seg;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   double* lse = a.lse + seg * a.lse_stride;
@@ -272,8 +272,8 @@ __global__ __launch_bounds__(256, NB == 1 ? 3 : 2) void colscore_kernel(CsArgs a
   if (!serve) {                           // uniform
     const int64_t base = (int64_t)(gs / a.H) * a.N * a.H * D + (int64_t)(gs % a.H) * D;
     for (int x = 0; x < NB; ++x)
-      if ((wg * NB + x) * 64 < a.N)
-        colscore_wide<D, ROWS>(a.q + base, a.k + base, a.N, a.H, a.sigma, lse, col, (wg * NB + x) * 64,
+      if ((x ? 2 * n_wg - 1 - wg : wg) * 64 < a.N)
+        colscore_wide<D, ROWS>(a.q + base, a.k + base, a.N, a.H, a.sigma, lse, col, (x ? 2 * n_wg - 1 - wg : wg) * 64,
                                *reinterpret_cast<CsWide<D>*>(slot0), *reinterpret_cast<CsMerge*>(slot0),
                                *reinterpret_cast<CsMerge*>(slot1));
     return;
@@ -282,13 +282,15 @@ __global__ __launch_bounds__(256, NB == 1 ? 3 : 2) void colscore_kernel(CsArgs a
   CsSlot<D, STG>& s1 = *reinterpret_cast<CsSlot<D, STG>*>(slot1);
   const int64_t own_side = (int64_t)(ROWS ? 0 : a.n_seg) + seg, oth_side = (int64_t)(ROWS ? a.n_seg : 0) + seg;
   const int nblk4 = (a.nblk + 3) & ~3;
-  const int first = wg * NB * 4;          // first own block of the workgroup; block first + 4 nb + wave is the wave's
+  // The workgroup's own blocks: four from block 4 wg on and, with two per wave, the four that lie as far from the
+  // other end, so that every workgroup has the same length of the causal triangle to do.
+  const int first = 4 * wg, second = 8 * n_wg - 4 - first;
   DigitBlock<D> own[NB];
   double f_own[NB], acc[NB];
   int ob[NB];
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
-    ob[nb] = first + 4 * nb + wave;
+    ob[nb] = (nb ? second : first) + wave;
     const int x = min(ob[nb], a.nblk - 1);
     const i32x4* src = reinterpret_cast<const i32x4*>(a.dig) + (own_side * a.nblk + x) * BLK + lane;
 #pragma unroll
@@ -300,7 +302,7 @@ __global__ __launch_bounds__(256, NB == 1 ? 3 : 2) void colscore_kernel(CsArgs a
     acc[nb] = 0.0;
   }
   const int s_begin = ROWS ? 0 : first;
-  const int s_end = ROWS ? min(a.nblk, first + 4 * NB) : a.nblk;
+  const int s_end = ROWS ? min(a.nblk, (NB == 2 ? second : first) + 4) : a.nblk;
   const rsrc_t digR = make_rsrc(a.dig + oth_side * a.nblk * BLK, (uint32_t)a.nblk * BLK * 16u);
   const rsrc_t expR = make_rsrc(a.exps + oth_side * nblk4, (uint32_t)nblk4 * 4u);
   const rsrc_t lseR = make_rsrc(lse, (uint32_t)a.nblk * 128u);
@@ -332,16 +334,34 @@ __global__ __launch_bounds__(256, NB == 1 ? 3 : 2) void colscore_kernel(CsArgs a
     }
     acc[nb] += (e[0] + e[1]) + (e[2] + e[3]);
   };
-  auto stage = [&](const CsSlot<D, STG>& sl, int t0, auto edge) __attribute__((always_inline)) {
-    digit_stage<D, NB, STG>(sl.dig, own, [&](const DigitSums& o, int x, int nb) __attribute__((always_inline)) {
-      add(sl, o, t0, x, nb, edge);
-    });
+  // own blocks FIRST .. FIRST + COUNT - 1 against a stage
+  auto stage = [&](const CsSlot<D, STG>& sl, int t0, auto first_own, auto count, bool full) __attribute__((always_inline)) {
+    if (full)
+      digit_stage<D, count.value, STG, first_own.value>(sl.dig, own, [&](const DigitSums& o, int x, int nb) __attribute__((always_inline)) {
+        add(sl, o, t0, x, nb, std::false_type{});
+      });
+    else
+      digit_stage<D, count.value, STG, first_own.value>(sl.dig, own, [&](const DigitSums& o, int x, int nb) __attribute__((always_inline)) {
+        add(sl, o, t0, x, nb, std::true_type{});
+      });
+  };
+  // whether some of a stage is visible to an own block, and all of it
+  auto seen = [&](int t0, int o) __attribute__((always_inline)) { return o < a.nblk && (ROWS ? t0 <= o : t0 + STG - 1 >= o); };
+  auto whole = [&](int t0, int o) __attribute__((always_inline)) {
+    return ROWS ? t0 + STG - 1 < o : t0 > o && (t0 + STG) * 16 <= a.N;
   };
   auto work = [&](const CsSlot<D, STG>& sl, int t0) __attribute__((always_inline)) {
-    if (ROWS ? t0 > ob[NB - 1] : t0 + STG - 1 < ob[0]) return;       // nothing of it is visible
-    const bool full = ROWS ? t0 + STG - 1 < ob[0] : t0 > ob[NB - 1] && (t0 + STG) * 16 <= a.N;
-    if (full) stage(sl, t0, std::false_type{});
-    else stage(sl, t0, std::true_type{});
+    constexpr std::integral_constant<int, 0> c0{};
+    constexpr std::integral_constant<int, 1> c1{};
+    if constexpr (NB == 1) {
+      if (seen(t0, ob[0])) stage(sl, t0, c0, c1, whole(t0, ob[0]));
+    } else {
+      // (the lower block sees a prefix of the columns that the upper one sees, and a superset of its rows)
+      constexpr std::integral_constant<int, 2> c2{};
+      constexpr int RARE = ROWS ? 0 : 1;
+      if (seen(t0, ob[RARE])) stage(sl, t0, c0, c2, whole(t0, ob[RARE]));
+      else if (seen(t0, ob[1 - RARE])) stage(sl, t0, std::integral_constant<int, 1 - RARE>{}, c1, whole(t0, ob[1 - RARE]));
+    }
   };
   fill(s0, s_begin);
   FL_WAIT_VM(0);
@@ -735,10 +755,13 @@ extern "C" int fl_column_scores(const uint16_t* q, const uint16_t* k_cache, int 
       int rc = check_launch("cs_digits_kernel");
       if (rc != FL_OK) return rc;
     }
-    // two blocks per wave halve the reads of the staged digits; with one, three workgroups share a CU and end more
-    // evenly: the statistic of 16 heads x 128 at N = 8192 (1024 workgroups of two) 1.46 ms against 1.51, at N = 4096 (512)
-    // 0.55 ms against 0.50
-    const bool wide = (int64_t)((a.nblk + 7) / 8) * a.n_seg >= 1024;
+    // Two blocks per wave, one from either end, make workgroups of equal length, two per CU, in rounds of 512; one block,
+    // the longest first, three per CU.  Two where their last round is at least three quarters full (or one of many).
+    // Two against one, 128-wide heads: N = 4096 x 16 (512 workgroups of two) 0.426 ms against 0.435, 8192 x 4 (512)
+    // 0.473 against 0.531, 8192 x 16 (1024) 1.451 against 1.471; 6000 x 16 (752) 0.838 against 0.812, 3000 x 16 (384)
+    // 0.311 against 0.281.
+    const int64_t pairs = (int64_t)((a.nblk + 7) / 8) * a.n_seg;
+    const bool wide = pairs >= 1536 || (pairs >= 512 && 4 * pairs >= 3 * 512 * ((pairs + 511) / 512));
     int rc;
     if (d == 128) rc = wide ? launch_colscore<128, 2>(a, st) : launch_colscore<128, 1>(a, st);
     else rc = wide ? launch_colscore<64, 2>(a, st) : launch_colscore<64, 1>(a, st);

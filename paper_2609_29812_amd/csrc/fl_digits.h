@@ -172,11 +172,12 @@ __device__ __forceinline__ double digit_dot(const DigitSums& o, int t) {
 
 constexpr int kDigStage = 4;              // 16-vector blocks staged in LDS per step
 
-// The kDigStage staged blocks (dig: as 16-byte pieces by block, digit 3 .. 0, 64 dims and lane) against a wave's NB own
-// ones: add(sums, staged block, own block) for each pair.  The products of a pair are issued between the vector
+// The STG staged blocks (dig: as 16-byte pieces by block, digit 3 .. 0, 64 dims and lane) against a wave's own ones
+// FIRST .. FIRST + NB - 1: add(sums, staged block, own block) for each pair.  The products of a pair are issued between the vector
 // instructions of the add before: a product's matrix cycles cover four of them.
-template <int D, int NB, int STG = kDigStage, typename Add>
-__device__ __forceinline__ void digit_stage(const uint4* dig, const DigitBlock<D> (&own)[NB], Add add) {
+template <int D, int NB, int STG = kDigStage, int FIRST = 0, int OWN, typename Add>
+__device__ __forceinline__ void digit_stage(const uint4* dig, const DigitBlock<D> (&own)[OWN], Add add) {
+  static_assert(FIRST + NB <= OWN, "own blocks FIRST .. FIRST + NB - 1");
   constexpr int KS = D / 64;
   const i32x4* src = reinterpret_cast<const i32x4*>(dig) + (threadIdx.x & 63);
   i32x4 d[4][KS];
@@ -190,10 +191,10 @@ __device__ __forceinline__ void digit_stage(const uint4* dig, const DigitBlock<D
 #pragma unroll
           for (int ks = 0; ks < KS; ++ks) d[s][ks] = src[((i + 1) / NB * 4 * KS + s * KS + ks) * 64];
       }
-      digit_sums<D>(d, own[(i + 1) % NB], o[(i + 1) & 1]);
+      digit_sums<D>(d, own[FIRST + (i + 1) % NB], o[(i + 1) & 1]);
     }
     if (i < 0) continue;
-    add(o[i & 1], i / NB, i % NB);
+    add(o[i & 1], i / NB, FIRST + i % NB);
 #pragma unroll
     for (int y = 0; y < 13 * KS; ++y) {
       __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
