@@ -354,9 +354,13 @@ const char* fl_attn_kernel_name(int pass, int k, int c_list, int window, int B, 
  * mass 1, summed over all rows of a prefill:
  *     col_key[b, h, j] = fp32( sum_{i >= j} exp(l_ij - lse_i) ),  l_ij = sigma * sum_e q_ie k_je,
  *     lse_i = log sum_{j <= i} exp(l_ij),   sigma = 1 / sqrt(d),
- * all in fp64 (products of bf16 values are exact in fp64).
+ * all in fp64.  The dot products are integer sums of the values' digits (exact, or their omissions bounded by half an
+ * fp32 ulp of an exponential), or fp64 products for a (batch, head) whose values these do not serve (infinities, NaN, a
+ * very wide range, exponents beyond +-330).
  *   q, k_cache : bf16 [B, N, H, d];  col_key : fp32 [B, H, N].
- *   ws         : at least fl_column_scores_ws(B, N, H) bytes (the fp64 row log-normalisers).
+ *   ws         : fl_column_scores_ws(B, N, H) bytes (the fp64 row log-normalisers, and the digits of up to about 256 MB
+ *                of (batch, head) pairs at a time).  With less, but at least 8 B N H bytes, or when q, k_cache or ws is
+ *                not 16-byte aligned, every pair takes fp64 products.
  * ---------------------------------------------------------------------------------------------- */
 size_t fl_column_scores_ws(int B, int N, int H);
 
@@ -446,9 +450,8 @@ int fl_decode_step_noalloc(const uint16_t* q, const uint16_t* k_cache, const uin
  *   cols_next  : int32 [B, H, ns + t_next] out, 0 <= t_next <= c_list - ns.
  *   ws         : at least fl_prune_columns_ws(B, H, k, c_list, n_sink) bytes (fp64 partial sums of
  *                256-row chunks; H * ceil(k / 256) <= 65535).
- * Three launches: the fp64 statistic per 256-row chunk of updated rows (dot products on fp64 matrix
- * instructions, 16 list entries per wave against query rows staged in LDS), the ordered sum of the chunks,
- * and the top-k.
+ * Three launches: the fp64 statistic per 256-row chunk of updated rows (dot products as in (4)), the ordered sum of
+ * the chunks, and the top-k.
  * ---------------------------------------------------------------------------------------------- */
 size_t fl_prune_columns_ws(int B, int H, int k, int c_list, int n_sink);
 
