@@ -673,16 +673,19 @@ struct CsWs {
   size_t dig, exps, stat, total;
 };
 constexpr size_t kCsGroupBytes = (size_t)256 << 20;
+constexpr size_t kCsGroupPairs = 65528;   // a grid's y extent, and a multiple of 8
 
 CsWs cs_ws(int B, int N, int H, int d) {
   const size_t nblk = ((size_t)N + 15) / 16;
   const size_t pair = 2 * nblk * 16 * (size_t)d * 4;
   const size_t all = (size_t)B * H;
   size_t n = kCsGroupBytes / pair;
-  n = n < 1 ? 1 : n > all ? all : n;
+  n = n < 1 ? 1 : n > kCsGroupPairs ? kCsGroupPairs : n;
+  const size_t most = n;
+  n = n > all ? all : n;
   const size_t groups = (all + n - 1) / n;
   n = (all + groups - 1) / groups;
-  if (n > 8 && n < all) n = (n + 7) / 8 * 8 <= kCsGroupBytes / pair ? (n + 7) / 8 * 8 : n / 8 * 8;
+  if (n > 8 && n < all) n = (n + 7) / 8 * 8 <= most ? (n + 7) / 8 * 8 : n / 8 * 8;
   CsWs w;
   w.n_seg = (int)n;
   size_t off = n * nblk * 16 * sizeof(double);          // lse [n_seg, 16 nblk]
@@ -735,7 +738,7 @@ extern "C" int fl_column_scores(const uint16_t* q, const uint16_t* k_cache, int 
   const bool aligned = ((reinterpret_cast<uintptr_t>(q) | reinterpret_cast<uintptr_t>(k_cache) | reinterpret_cast<uintptr_t>(ws)) & 15) == 0;
   const bool digits = aligned && ws_bytes >= w.total && (int64_t)a.nblk * 64 * d < ((int64_t)1 << 31);
   const int all = B * H;
-  int step = all;
+  int step = std::min<int>(all, kCsGroupPairs);
   a.lse_stride = N;
   if (digits) {
     char* base = static_cast<char*>(ws);

@@ -74,6 +74,13 @@ def test_two_blocks_per_wave(F, d):
     _check(F, "normal", B, N, H, d, got, q, k, (0, 9))
 
 
+def test_many_heads(F):
+    """More (batch, head) pairs than a grid's y extent; one position each, whose only probability is 1."""
+    B, N, H, d = 35000, 1, 2, 64
+    x = torch.randn(B, N, H, d, device="cuda").to(torch.bfloat16)
+    assert bool((F.column_scores(x, x) == 1.0).all())
+
+
 @pytest.mark.parametrize("kind", ["tiny-q", "tiny-k", "tiny-both", "zeros", "large", "outlier", "wide"])
 @pytest.mark.parametrize("d", [64, 128])
 def test_values(F, kind, d):
