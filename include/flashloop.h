@@ -396,6 +396,8 @@ int fl_select_columns(const float* col_key, int B, int H, int N, int n_sink, int
  *   lse               : optional fp32 [B, H]: L.
  *   c_next            : 0 <= c_next <= |S| (0: no selection; the outputs below may then be NULL).
  *   cols_next         : int32 [B, H, c_next];  mass_next : fp32 [B, H];  sub_next : fp32 [B, H, d].
+ *                       mass_next may be mass and sub_next may be sub (updated in place; then one launch more where one
+ *                       workgroup selects); cols_next must not overlap cols.
  *   ws                : at least fl_decode_step_ws(B, T, H, d, c, c_next) bytes (|S| <= 65536).
  * Two or three launches: chunked logits (with their fp32 ranking keys) and weighted V rows; then, per (b, h),
  * a workgroup that merges them into L and the output and workgroups that form S', m' and sub' (c_next = |S| keeps

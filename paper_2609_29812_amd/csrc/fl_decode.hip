@@ -192,11 +192,13 @@ __global__ __launch_bounds__(256) void decode_partial_kernel(DecodeArgs a) {
 // ---- finalize ------------------------------------------------------------------------------------------
 // Workgroup y = 0 of each (b, h) merges the chunks into L and the output; when the next loop keeps every column
 // (c_next = n) it also writes the columns themselves, m' = m (the probabilities over S sum to m) and sub' = the
-// add term just formed.  Otherwise the workgroups y = 1 .. n_sel select the next loop's columns and sum their
-// probabilities and values: each runs the radix top-k of fl_topk.h over all keys, writes its share of the selected
+// add term just formed.  Otherwise the workgroups y = 1 .. n_sel (the grid starts at y0) select the next loop's columns
+// and sum their probabilities and values: each runs the radix top-k of fl_topk.h over all keys, writes its share of the selected
 // positions (ascending) and gathers their logits and V rows (ids and weights in LDS, every V load issued before any
 // use).  With one of them the positions go through the workspace in windows of kSelWin; with more, each has one
-// window in LDS, and decode_sum_kernel adds their sums in order (deterministic).
+// window in LDS, and decode_sum_kernel adds their sums in order (deterministic).  The merge reads m and sub, which the
+// one selecting workgroup replaces by m' and sub' where a caller updates them in place: then the two are launched one
+// after the other (more selecting workgroups write sums of their own, and the merge alone touches m and sub).
 //
 // Bound by latency: a top-k over 32K keys takes about 20 us on one workgroup however few of them run, and the
 // gather of 2048 rows by one workgroup as long again.  At 16 heads over 32K columns, c_next = 2048, one workgroup for
@@ -251,7 +253,7 @@ __device__ __forceinline__ void decode_merge(const DecodeArgs& a, int bh, double
 }
 
 template <int D, int M, int NH>
-__global__ __launch_bounds__(kTopkThreads) void decode_finalize_kernel(DecodeArgs a) {
+__global__ __launch_bounds__(kTopkThreads) void decode_finalize_kernel(DecodeArgs a, int n_sel, int y0) {
   constexpr int NW = kTopkThreads / 64;      // waves
   constexpr int LPC = D / 8;                 // lanes per V row (16 bytes each)
   constexpr int CPW = 64 / LPC;              // rows per wave instruction
@@ -272,12 +274,12 @@ __global__ __launch_bounds__(kTopkThreads) void decode_finalize_kernel(DecodeArg
   const int b = bh / a.H, h = bh % a.H;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const double m = a.cols ? (double)a.mass[bh] : 1.0;
-  if (blockIdx.y == 0) {                     // uniform
+  const int y = (int)blockIdx.y + y0 - 1;    // -1: the merge
+  if (y < 0) {                               // uniform
     decode_merge<D>(a, bh, m, s_f, s_acc);
     return;
   }
   // this workgroup's share [lo0, hi0) of the selected positions
-  const int n_sel = gridDim.y - 1, y = blockIdx.y - 1;
   const int share = (a.c_next + n_sel - 1) / n_sel;
   const int lo0 = y * share, hi0 = min(a.c_next, lo0 + share);
   int32_t* sel = const_cast<int32_t*>(a.sel) + (int64_t)bh * a.c_next;
@@ -385,6 +387,12 @@ static int select_workgroups(int bh, int d, int n, int c_next) {
   return most;
 }
 
+// whether two arrays of the same size share memory
+static bool overlap(const void* a, const void* b, size_t bytes) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return x < y + bytes && y < x + bytes;
+}
+
 // workspace regions, each 256-byte aligned
 struct DecodeWs {
   size_t logit, pmax, psum, pacc, key, sel, total;
@@ -476,12 +484,21 @@ static int decode_step(const char* fn, bool use_scratch, const uint16_t* q, cons
   a.part_mass = reinterpret_cast<double*>(base + L.sel);
   a.part_sub = reinterpret_cast<float*>(a.part_mass + (int64_t)BH * n_sel);
   const int keys = n_sel > 0 ? n : 0;
-  const dim3 gf(BH, 1 + n_sel);
-#define FL_FIN(MM, HH)                                                                        \
-  do {                                                                                        \
-    if (d == 128) decode_finalize_kernel<128, MM, HH><<<gf, kTopkThreads, 0, st>>>(a);        \
-    else decode_finalize_kernel<64, MM, HH><<<gf, kTopkThreads, 0, st>>>(a);                  \
+  int y0 = 0;
+  dim3 gf(BH, 1 + n_sel);
+#define FL_FIN(MM, HH)                                                                              \
+  do {                                                                                              \
+    if (d == 128) decode_finalize_kernel<128, MM, HH><<<gf, kTopkThreads, 0, st>>>(a, n_sel, y0);   \
+    else decode_finalize_kernel<64, MM, HH><<<gf, kTopkThreads, 0, st>>>(a, n_sel, y0);             \
   } while (0)
+  if (n_sel == 1 && !dense &&
+      (overlap(sub, sub_next, (size_t)BH * d * sizeof(float)) || overlap(mass, mass_next, (size_t)BH * sizeof(float)))) {
+    gf.y = 1;
+    FL_FIN(1, 1);                          // the merge
+    rc = check_launch("decode_finalize_kernel(merge)");
+    if (rc != FL_OK) return rc;
+    y0 = 1;
+  }
   if (keys <= 1024) FL_FIN(1, 1);
   else if (keys <= 2048) FL_FIN(2, 1);
   else if (keys <= 4096) FL_FIN(4, 1);

@@ -106,3 +106,28 @@ def test_decode_rejects_bad_arguments(F):
     cols = torch.zeros(1, 2, 3, dtype=torch.int32, device="cuda")
     with pytest.raises(F.FlashLoopError, match="mass"):
         F.decode_step(q, kc, kc, cols, None, None, o, 2)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("B,H,budgets", [(2, 3, [180, 120, 120, 37]),      # one selecting workgroup, then every column kept
+                                         (1, 2, [900, 600, 280]),          # several selecting workgroups
+                                         (9, 16, [640, 400, 300])])        # one of them, as more pairs fill the CUs
+def test_decode_in_place(F, B, H, d, budgets):
+    """Masses and subtract terms updated in place give the bits of separate outputs."""
+    T = 1100
+    rng = np.random.default_rng(B + d)
+    k, v = (up_bf16(_bf16(rng, (B, T, H, d))) for _ in range(2))
+    qs = [up_bf16(_bf16(rng, (B, H, d))) for _ in budgets]
+
+    def chain(in_place):
+        o = torch.zeros(B, H, d, device="cuda")
+        cols, mass, sub = None, torch.empty(B, H, device="cuda"), torch.empty(B, H, d, device="cuda")
+        for r, (q, c) in enumerate(zip(qs, budgets)):
+            nxt = (torch.empty(B, H, c, dtype=torch.int32, device="cuda"),
+                   mass if in_place else torch.empty_like(mass), sub if in_place else torch.empty_like(sub))
+            args = (None, None, None) if r == 0 else (cols, mass, sub)
+            cols, mass, sub = F.decode_step(q, k, v, *args, o, c, n_sink=4, window=8, out=nxt)
+        return [down(t) for t in (o, cols, mass, sub)]
+
+    for got, want, what in zip(chain(True), chain(False), ("o", "columns", "mass", "subtract term")):
+        assert np.array_equal(got, want), what
