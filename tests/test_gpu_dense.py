@@ -48,3 +48,19 @@ def test_whole_rows(F, N, d, B, H):
 def test_sharp_rows(F):
     """Logits that move the softmax reference many times."""
     _check(F, 1, 700, 2, 128, [(0, 0), (0, 1)], scale=8.0)
+
+
+@pytest.mark.parametrize("d,B,H", [(128, 1, 3), (64, 1, 3), (128, 8, 64), (64, 16, 64)])   # split columns, whole rows
+@pytest.mark.parametrize("j", [40, 70, 100, 127, 140])
+def test_value_out_of_range(F, d, B, H, j):
+    """A value that is not finite in fp16 reaches the 32-row group of its own position and the rows after, no earlier
+    ones: those keep the bits of finite values."""
+    N = 150
+    g = torch.Generator(device="cuda").manual_seed(j)
+    q, k, v = (torch.randn(B, N, H, d, device="cuda", generator=g).to(torch.bfloat16) for _ in range(3))
+    want, want_lse = F.dense_attn(q, k, v)
+    v[:, j] = torch.tensor([float("inf"), float("nan"), 1e6, -1e6], device="cuda").to(torch.bfloat16).repeat(d // 4)
+    got, lse = F.dense_attn(q, k, v)
+    lo = j // 32 * 32
+    assert torch.equal(got[:, :lo], want[:, :lo])
+    assert torch.equal(lse, want_lse)
