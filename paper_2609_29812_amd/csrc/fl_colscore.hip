@@ -708,12 +708,12 @@ int launch_colscore(const CsArgs& a, hipStream_t st) {
 }
 }  // namespace
 
-// (the head dimension is not an argument: sized for 128)
+// The head dimension is not an argument, so the larger of the two layouts: where the pairs take more than one group,
+// 64-wide heads put up to twice as many into each, with their normalisers, exponents and figures.
 extern "C" size_t fl_column_scores_ws(int B, int N, int H) {
   if (B < 1 || N < 1 || H < 1) return 0;
   const size_t rows = (size_t)B * (size_t)H * (size_t)N * sizeof(double);
-  const size_t digits = cs_ws(B, N, H, 128).total;
-  return digits > rows ? digits : rows;
+  return std::max(rows, std::max(cs_ws(B, N, H, 64).total, cs_ws(B, N, H, 128).total));
 }
 
 extern "C" int fl_column_scores(const uint16_t* q, const uint16_t* k_cache, int B, int N, int H, int d,

@@ -73,3 +73,17 @@ def new_rows(out, name, cache):
     idx = down(out["idx"])
     c = down_bits16(cache)
     return np.stack([c[b, idx[b]] for b in range(idx.shape[0])])
+
+
+def column_layout(B, N, H, d):
+    """The dense column statistic's workspace with digits: (pairs of a group, bytes).  Per pair of a group the rows'
+    normalisers (8 bytes a row of 16-row blocks), the digits of q and k (4 bytes an element), and per block of either
+    side its exponent (rounded up to four blocks) and its figures."""
+    nblk = -(-N // 16)
+    pair, pairs = 2 * nblk * 16 * d * 4, B * H
+    most = min(max((256 << 20) // pair, 1), 65528)
+    groups = -(-pairs // min(most, pairs))
+    n = -(-pairs // groups)
+    if 8 < n < pairs:
+        n = -(-n // 8) * 8 if -(-n // 8) * 8 <= most else n // 8 * 8
+    return n, n * (nblk * 128 + pair + 2 * 4 * (-(-nblk // 4) * 4) + 2 * nblk * 16)

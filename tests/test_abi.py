@@ -7,6 +7,7 @@ import re
 
 import pytest
 
+from gpu_util import column_layout
 from paper_2609_29812_amd import flashloop as fl
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -56,6 +57,13 @@ def test_workspace_queries(lib):
     # list pruning: fp64 partial sums per 256-row chunk of the updated rows and per non-sink entry
     assert lib.fl_prune_columns_ws(1, 16, 1638, 1536, 4) == 16 * 7 * 1532 * 8
     assert lib.fl_prune_columns_ws(2, 3, 0, 10, 20) == 0          # all sinks: nothing to rank
+    # dense column statistic: digits of either head width (the query is not told which), one group of pairs and many
+    for B in (1, 2, 3, 4, 8, 35000):
+        for H in (1, 2, 5, 12, 16, 64):
+            for N in (1, 15, 16, 17, 1000, 4096, 6000, 8192, 12000, 16384, 16400, 20000, 32768, 65536):
+                if B * H * N < 1 << 31:
+                    want = max(8 * B * H * N, *(column_layout(B, N, H, d)[1] for d in (64, 128)))
+                    assert lib.fl_column_scores_ws(B, N, H) == want, (B, N, H)
 
 
 def _attn(lib, **kw):

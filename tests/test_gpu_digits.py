@@ -12,7 +12,7 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_util import assert_keys_close, down, say, up_bf16
+from gpu_util import assert_keys_close, column_layout, down, say, up_bf16
 from oracle import attention as att
 from oracle import prune
 from oracle.numerics import bf16_to_f64, f32_to_bf16
@@ -48,6 +48,37 @@ def _inputs(kind, B, N, H, d):
     return f32_to_bf16(q), f32_to_bf16(k)
 
 
+def _scores(F, q, k, ws_bytes=None):
+    """fl_column_scores with the workspace that the query asks for (or ws_bytes): the keys, and per (batch, head) of the
+    last group of pairs whether the digits served it: they leave base-2 row normalisers at the workspace's start, the
+    fp64 products natural ones."""
+    B, N, H, d = q.shape
+    n, need = column_layout(B, N, H, d)
+    size = F.load().fl_column_scores_ws(B, N, H) if ws_bytes is None else ws_bytes
+    ws = torch.zeros(size, dtype=torch.uint8, device="cuda")
+    key = torch.empty(B, H, N, device="cuda")
+    p = lambda t: ctypes.c_void_p(t.data_ptr())  # noqa: E731
+    rc = F.load().fl_column_scores(p(q), p(k), B, N, H, d, p(key), p(ws), size,
+                                   ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == 0
+    pairs = B * H
+    first, stride = (pairs - 1) // n * n, -(-N // 16) * 16
+    if size < need:
+        first, stride = 0, N
+    lse = ws[:(pairs - first) * stride * 8].view(torch.float64).view(-1, stride)[:, :N]
+    rows = torch.linspace(0, N - 1, min(N, 9), device="cuda").round().long()
+    served = []
+    for x in range(first, pairs):
+        b, h = divmod(x, H)
+        want = torch.stack([torch.logsumexp(k[b, :i + 1, h].double() @ q[b, i, h].double() / d ** 0.5, 0)
+                            for i in rows.tolist()])
+        got = lse[x - first, rows]
+        by2 = bool(((got - want * 1.4426950408889634).abs() <= 1e-6 * (1 + want.abs())).all())
+        assert by2 or bool(((got - want).abs() <= 1e-9 * (1 + want.abs())).all()) or not bool(want.isfinite().all())
+        served.append(by2)
+    return down(key), served
+
+
 def _check(F, kind, B, N, H, d, got, q, k, heads):
     for b in range(B):
         for h in heads:
@@ -72,6 +103,28 @@ def test_two_blocks_per_wave(F, d):
     q, k = _inputs("normal", B, N, H, d)
     got = down(F.column_scores(up_bf16(q), up_bf16(k)))
     _check(F, "normal", B, N, H, d, got, q, k, (0, 9))
+
+
+def _assert_sums(key, N):
+    """Each row's probabilities sum to 1: N in all, to the fp32 rounding of the keys."""
+    total = key.astype(np.float64).sum(-1)
+    assert np.all(np.abs(total - N) <= 2.0 ** -22 * N), total
+
+
+@pytest.mark.parametrize("B,N,H,d,groups", [(1, 16400, 16, 64, 1),      # (two groups of 128-wide heads)
+                                            (9, 8177, 9, 64, 2), (1, 16400, 17, 128, 3)])
+def test_groups(F, B, N, H, d, groups):
+    """Long prompts and batches, whose pairs take one group of the workspace or more, the last one smaller: with the
+    workspace that the query asks for the digits serve all of them."""
+    assert -(-B * H // column_layout(B, N, H, d)[0]) == groups
+    g = torch.Generator(device="cuda").manual_seed(N)
+    q, k = (torch.randn(B, N, H, d, device="cuda", generator=g).to(torch.bfloat16) for _ in range(2))
+    key, served = _scores(F, q, k)
+    assert all(served)
+    _assert_sums(key, N)
+    for b, h in ((0, 0), (B - 1, H - 1)):
+        alone = down(F.column_scores(*(x[b:b + 1, :, h:h + 1].contiguous() for x in (q, k))))
+        assert_keys_close(key[b, h], alone[0, 0], f"b={b} h={h}")
 
 
 def test_many_heads(F):
@@ -105,16 +158,9 @@ def test_not_finite_takes_fp64(F):
 def _small_workspace(F, q, k):
     """fl_column_scores with room for the rows' log-normalisers only (fp64 products for every head)."""
     B, N, H, d = q.shape
-    dq, dk = up_bf16(q), up_bf16(k)
-    ws = torch.empty(B * H * N * 8, dtype=torch.uint8, device="cuda")
-    assert F.load().fl_column_scores_ws(B, N, H) > ws.numel()
-    key = torch.empty(B, H, N, device="cuda")
-    p = lambda t: ctypes.c_void_p(t.data_ptr())  # noqa: E731
-    rc = F.load().fl_column_scores(p(dq), p(dk), B, N, H, d, p(key), p(ws), ws.numel(),
-                                   ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
-    assert rc == 0
-    torch.cuda.synchronize()
-    return down(key)
+    key, served = _scores(F, up_bf16(q), up_bf16(k), B * H * N * 8)
+    assert not any(served)
+    return key
 
 
 def test_small_workspace(F):
