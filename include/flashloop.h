@@ -354,9 +354,10 @@ const char* fl_attn_kernel_name(int pass, int k, int c_list, int window, int B, 
  * mass 1, summed over all rows of a prefill:
  *     col_key[b, h, j] = fp32( sum_{i >= j} exp(l_ij - lse_i) ),  l_ij = sigma * sum_e q_ie k_je,
  *     lse_i = log sum_{j <= i} exp(l_ij),   sigma = 1 / sqrt(d),
- * all in fp64.  The dot products are integer sums of the values' digits (exact, or their omissions bounded by half an
- * fp32 ulp of an exponential), or fp64 products for a (batch, head) whose values these do not serve (infinities, NaN, a
- * very wide range, exponents beyond +-330).
+ * all in 64 bits.  The dot products are integer sums of the values' digits where what these leave out of the values
+ * (the smallest elements of blocks of 16 vectors, bounded from the values) moves no exponent by more than 2^-25, so no
+ * key by more than 2^-24 of itself before it is rounded; or fp64 products for a (batch, head) whose values the digits do
+ * not serve (infinities, NaN, a wider range, |q| |k| sigma beyond 330).
  *   q, k_cache : bf16 [B, N, H, d];  col_key : fp32 [B, H, N].
  *   ws         : fl_column_scores_ws(B, N, H) bytes (the fp64 row log-normalisers, and the digits of up to about 256 MB
  *                of (batch, head) pairs at a time).  With less, but at least 8 B N H bytes, or when q, k_cache or ws is

@@ -1,11 +1,12 @@
 // Dot products of bf16 vectors as integer sums on the i8 matrix instructions, for the fp64 statistics.
 //
-// Sixteen vectors with max|x| < 2^E are taken as integers X_e = rint(x_e 2^(30 - E)), |X| <= 2^30, and X as four
-// balanced base-256 digits: X = sum_s d_s 256^s, d_s in [-128, 127] (|d_3| <= 64).  A bf16 value has 8 significant
-// bits, so X_e is exact unless 0 < |x_e| < 2^(E - 22).  The dot product is the sum over digit pairs (s, t) of
+// Sixteen vectors are taken as integers X_e = rint(x_e / u), u = 2^(E - 31) a power of two with |X| <= 0x7F7F7F7F (2^E
+// the first power of two above max|x|, or the one after where max|x| has a significand of eight ones), and X as four
+// balanced base-256 digits: X = sum_s d_s 256^s, d_s in [-128, 127].  A bf16 value has 8 significant
+// bits, so X_e is exact unless 0 < |x_e| < 2^(E - 23).  The dot product is the sum over digit pairs (s, t) of
 // 256^(s + t) sum_e d_s d'_t, each inner sum exact in int32, and pairs of one weight share an accumulator.  The
-// pairs of weight 256 and 1 (a digit 0, which only elements below 2^(E - 14) have, with a digit 1 or 0) are left out:
-// at most 2^-36 of 2^E 2^E' for an element, counted in digits_serve.
+// pairs of weight 256 and 1 (a digit 0, which only elements below 2^(E - 15) have, with a digit 1 or 0) are left out.
+// What these and the rounded elements can amount to is bounded from the values at hand (DigitStat, digits_serve).
 //
 // Thirteen 8-bit products at twice the bf16 rate replace the fp64 product at 1/32 of it (2.5 PFLOP/s against
 // 78.6 TFLOP/s): about 5 times the rate of the fp64 matrix instructions for the same sums.
@@ -16,12 +17,21 @@ namespace fl {
 
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 
-// What 16 vectors hold: the largest sum over one vector of the absolute values that the digits leave out, the bound
-// of their elements (2^E; +inf if one is not finite) and their largest 2-norm.
+// What 16 vectors hold: the largest sum over one vector of the absolute roundings |x_e - u X_e|, the largest 2-norms of a
+// vector's digits 0 and 1 (times u), the largest |x_e| (+inf if one is not finite) and the largest 2-norm of a vector.
 struct DigitStat {
-  float res, top, norm;
-  int e;                    // E
+  float res, low0, low1, top, norm;
+  int e;                    // u = 2^e
 };
+
+// the larger of each figure (not of the exponents)
+__device__ __forceinline__ void join_stat(DigitStat& a, const DigitStat& b) {
+  a.res = fmaxf(a.res, b.res);
+  a.low0 = fmaxf(a.low0, b.low0);
+  a.low1 = fmaxf(a.low1, b.low1);
+  a.top = fmaxf(a.top, b.top);
+  a.norm = fmaxf(a.norm, b.norm);
+}
 
 // Digits of 8 consecutive elements per uint4 of bf16 pairs: out[s][0..1] = digit s of elements 0-3 and 4-7.
 __device__ __forceinline__ void digits8(uint4 w, float scale, uint32_t (&out)[4][2], float& res) {
@@ -55,10 +65,10 @@ __device__ __forceinline__ uint32_t max_abs_bits(uint4 w, uint32_t m) {
   return m;
 }
 
-// E of a vector whose largest |bf16| pattern is m, kept where the scale 2^(30 - E) is a normal float; 129 for
-// infinities and NaN.
-__device__ __forceinline__ int digit_exponent(uint32_t m) { return max((int)(m >> 7) - 126, -90); }
-__device__ __forceinline__ float digit_scale(int e) { return __uint_as_float((uint32_t)(157 - e) << 23); }   // 2^(30 - e)
+// The exponent of u for a largest |bf16| pattern of m, kept where u and 1 / u are normal floats (also for infinities and
+// NaN, whose digits are not used).
+__device__ __forceinline__ int digit_exponent(uint32_t m) { return max((int)((m + 1) >> 7) - 126, -90) - 31; }
+__device__ __forceinline__ float pow2f(int e) { return __uint_as_float((uint32_t)(127 + e) << 23); }
 
 // Digits of 16 vectors as one wave holds them: lane (l16, g) = (lane % 16, lane / 16) holds dims 64 ks + 16 g ..
 // + 15 of vector l16 (any split of the dims over g serves, being the same on both sides of a product).
@@ -90,8 +100,9 @@ __device__ __forceinline__ DigitBlock<D> make_digits(const uint4 (&w)[2 * (D / 6
   m = (uint32_t)row4_max(row16_max((float)m));              // (15 bits: exact as floats)
   const int e = digit_exponent(m);
   const bool finite = m < 0x7F80u;
-  const float scale = digit_scale(e);
+  const float scale = pow2f(-e);
   float res = 0.0f, n2 = 0.0f;
+  int q0 = 0, q1 = 0;                       // squares of the digits 0 and 1
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) {
 #pragma unroll
@@ -103,6 +114,11 @@ __device__ __forceinline__ DigitBlock<D> make_digits(const uint4 (&w)[2 * (D / 6
         o.d[s][ks][2 * half] = (int)q[3 - s][0];
         o.d[s][ks][2 * half + 1] = (int)q[3 - s][1];
       }
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        q0 = __builtin_amdgcn_sdot4((int)q[0][t], (int)q[0][t], q0, false);
+        q1 = __builtin_amdgcn_sdot4((int)q[1][t], (int)q[1][t], q1, false);
+      }
       const uint32_t ws[4] = {w[2 * ks + half].x, w[2 * ks + half].y, w[2 * ks + half].z, w[2 * ks + half].w};
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
@@ -111,27 +127,30 @@ __device__ __forceinline__ DigitBlock<D> make_digits(const uint4 (&w)[2 * (D / 6
       }
     }
   }
-  const float unit = __uint_as_float((uint32_t)max(e - 30 + 127, 1) << 23);     // 2^(e - 30), at least 2^-126
+  const float unit = pow2f(e);
   res = row16_max(row4_add(res));
-  const float norm = sqrtf(row16_max(row4_add(n2)));
-  stat.res = finite ? res * unit : INFINITY;
-  stat.top = finite ? unit * 0x1p30f : INFINITY;
-  stat.norm = finite ? norm : INFINITY;
+  stat.res = res * unit;
+  // (square roots to an ulp: digits_serve allows for it; sums of at most 128 squares of digits are exact as floats)
+  stat.low0 = __builtin_amdgcn_sqrtf(row16_max(row4_add((float)q0))) * unit;
+  stat.low1 = __builtin_amdgcn_sqrtf(row16_max(row4_add((float)q1))) * unit;
+  stat.top = finite ? __uint_as_float(m << 16) : INFINITY;
+  stat.norm = finite ? __builtin_amdgcn_sqrtf(row16_max(row4_add(n2))) : INFINITY;
   stat.e = e;
   return o;
 }
 
 // Whether the digits serve all dot products between the vectors of two sides: with `scale` the factor from dot
-// product to natural exponent, what the digits leave out moves an exponent by at most 2^-24 (half an ulp of the
-// fp32 results), and no exponent leaves +-330 (its base-2 form stays far inside the doubles' range without a running
-// maximum).  False for infinities and NaN.
-__device__ __forceinline__ bool digits_serve(const DigitStat& a, const DigitStat& b, int d, double scale) {
-  // the products left out: |d_0 d'_1 256 + d_1 d'_0 256 + d_0 d'_0| <= 2^23.01 per element, in units of
-  // 2^(E + E' - 60); rare where the elements are not all tiny, and bounded here as if every one had them
-  const double pairs = d * 0x1.02p-37 * (double)a.top * b.top;
-  const double off = ((double)a.res * b.top + (double)b.res * a.top + pairs) * scale;
-  const double most = (double)a.norm * b.norm * scale;
-  return off <= 0x1p-24 && most <= 330.0;
+// product to natural exponent, what the digits leave out moves an exponent by at most 2^-25, so exp(l - lse) and the
+// sums of it by at most 2^-24 of themselves (half an fp32 ulp at most), and no exponent leaves +-330 (its base-2 form
+// stays far inside the doubles' range without a running maximum).  False for infinities and NaN.
+// The pairs of digits left out are bounded by the norms of those digits, the roundings of one side by their sum times
+// the largest element of the other.  For standard normal vectors of 128 dims, 32K of either side, the two come to
+// 2^-34 and 2^-30; with one key channel offset by 32 to 2^-30 and 2^-26.5.
+__device__ __forceinline__ bool digits_serve(const DigitStat& a, const DigitStat& b, float scale) {
+  const float pairs = 256.0f * (a.low0 * b.low1 + a.low1 * b.low0) + a.low0 * b.low0;
+  const float off = (a.res * b.top + b.res * (a.top + a.res) + pairs) * scale;
+  const float most = a.norm * b.norm * scale;
+  return off <= 0x1p-25f * 0.9999f && most <= 330.0f;     // (beyond fp32's range: false)
 }
 
 // Integer sums of a 16 x 16 block of dot products (rows 4 g + t of `a`, column l16 of `b`), by weight 256^(n + 2).
@@ -163,8 +182,9 @@ __device__ __forceinline__ void digit_sums(const i32x4 (&a)[4][D / 64], const Di
   o.s[0] = s2; o.s[1] = s3; o.s[2] = s4; o.s[3] = s5; o.s[4] = s6;
 }
 
-// The lane's dot product t in units of 2^16 2^(E + E' - 60).  |s6| <= 2^19, |s4| < 2^22 and |s3| < 2^23 for 128
-// dims, so each shifted pair fits int32; the doubles hold the sum exactly (below 2^52).
+// The lane's dot product t in units of 2^16 u u'.  |s6| <= 2^21, |s4| < 2^22.6 and |s3| <= 2^23 for 128 dims, so each
+// shifted pair fits int32; the doubles hold the sum exactly below 2^53 (beyond only for vectors whose elements are nearly
+// all at the bound, then rounded once).
 __device__ __forceinline__ double digit_dot(const DigitSums& o, int t) {
   const double p = fma((double)(o.s[4][t] * 256 + o.s[3][t]), 65536.0, (double)(o.s[2][t] * 256 + o.s[1][t]));
   return fma(p, 256.0, (double)o.s[0][t]);

@@ -86,4 +86,4 @@ def column_layout(B, N, H, d):
     n = -(-pairs // groups)
     if 8 < n < pairs:
         n = -(-n // 8) * 8 if -(-n // 8) * 8 <= most else n // 8 * 8
-    return n, n * (nblk * 128 + pair + 2 * 4 * (-(-nblk // 4) * 4) + 2 * nblk * 16)
+    return n, n * (nblk * 128 + pair + 2 * 4 * (-(-nblk // 4) * 4) + 2 * nblk * 24)

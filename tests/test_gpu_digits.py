@@ -1,10 +1,12 @@
 """GPU parity of the fp64 column and list statistics on integer digits (fl_digits.h) where its tiles and ranges end.
 
-Keys within one fp32 ulp of the oracle's fp64 statistic rounded to fp32: the digits hold the dot products to better
-than 2^-24 of an exponent, or the (batch, head) takes the fp64 products.  Lengths: around the 16-vector blocks, the
-64-vector stages and both workgroup sizes.  Values: standard normal; elements far below the largest of their block
-(digit 0) on either and on both sides; zero vectors; magnitudes whose exponents leave the digits' range, an infinity
-and an outlier beside tiny elements (fp64 products); and a workspace that holds no digits.
+Keys within one fp32 ulp of the oracle's fp64 statistic rounded to fp32: the digits hold an exponent to 2^-25, so a sum
+of exponentials to 2^-24 of itself before it is rounded (in the worst case; typically some 2^-30), or the (batch, head)
+takes the fp64 products.  Which of the two served is read off the workspace.  Lengths: around the 16-vector blocks, the
+64-vector stages and both workgroup sizes, and several groups of pairs.  Values: normal of several deviations; channels
+far from the others; elements far below the largest of their block (digit 0) on either and on both sides; zero vectors;
+exponents close to the digits' bound and beyond it; an infinity and an outlier beside tiny elements (fp64 products); and
+a workspace that holds no digits.
 """
 import ctypes
 
@@ -37,7 +39,17 @@ def _inputs(kind, B, N, H, d):
         k = np.where(tiny > 0, k * tiny, k)
     if kind == "zeros":
         q[:, ::3], k[:, 1::2] = 0, 0
-    if kind == "large":                       # exponents in the hundreds
+    if kind[0] == "s" and kind[1:].isdigit():
+        q, k = q * int(kind[1:]), k * int(kind[1:])
+    if kind == "channel":
+        k[..., 3] += 32
+    if kind == "channels":
+        k[..., 3] += 16
+        q[..., 5] += 8
+    if kind == "sharp":                       # exponents of 280 for rows and columns that are alike, of either sign
+        k = q * rng.choice(np.float32([-1, 1]), (B, N, H, 1))
+        q, k = (x * (np.sqrt(280.0 * np.sqrt(d)) / np.linalg.norm(x, axis=-1, keepdims=True)) for x in (q, k))
+    if kind == "large":                       # exponents beyond the digits' bound
         q, k = q * 12, k * 12
     if kind == "outlier":                     # elements that the digits of their block do not hold
         k[:, :, 0, 3] *= 5000
@@ -97,11 +109,13 @@ def test_lengths(F, B, N, H, d):
 
 
 @pytest.mark.parametrize("d", [64, 128])
-def test_two_blocks_per_wave(F, d):
-    """128-vector workgroups (at least 1024 of them), the last one partial."""
-    B, N, H = 4, 2047, 16
+@pytest.mark.parametrize("N", [2047, 1936, 1970])     # 128, 121 and 124 blocks: upper halves whole, of one block, and absent
+def test_two_blocks_per_wave(F, N, d):
+    """128-vector workgroups (1024 of them)."""
+    B, H = 4, 16
     q, k = _inputs("normal", B, N, H, d)
-    got = down(F.column_scores(up_bf16(q), up_bf16(k)))
+    got, served = _scores(F, up_bf16(q), up_bf16(k))
+    assert all(served)
     _check(F, "normal", B, N, H, d, got, q, k, (0, 9))
 
 
@@ -134,13 +148,29 @@ def test_many_heads(F):
     assert bool((F.column_scores(x, x) == 1.0).all())
 
 
-@pytest.mark.parametrize("kind", ["tiny-q", "tiny-k", "tiny-both", "zeros", "large", "outlier", "wide"])
+@pytest.mark.parametrize("kind,serves", [("normal", True), ("s2", True), ("s3", True), ("s4", True), ("channel", True),
+                                         ("channels", True), ("tiny-q", True), ("tiny-k", True), ("tiny-both", True),
+                                         ("zeros", True), ("sharp", True), ("large", False), ("outlier", False),
+                                         ("wide", False)])
 @pytest.mark.parametrize("d", [64, 128])
-def test_values(F, kind, d):
+def test_values(F, kind, serves, d):
     B, N, H = 1, 300, 2
     q, k = _inputs(kind, B, N, H, d)
-    got = down(F.column_scores(up_bf16(q), up_bf16(k)))
+    got, served = _scores(F, up_bf16(q), up_bf16(k))
+    assert served == [serves, serves or kind == "outlier"]      # (the outlier is in the first head)
     _check(F, kind, B, N, H, d, got, q, k, range(H))
+
+
+@pytest.mark.parametrize("kind", ["s3", "s4", "channel"])
+def test_values_of_a_long_prompt(F, kind):
+    """Many vectors, with the rare elements that the digits round, in 128-vector workgroups: the digits serve them."""
+    B, N, H, d = 1, 8192, 16, 128
+    q, k = (up_bf16(x) for x in _inputs(kind, B, N, H, d))
+    got, served = _scores(F, q, k)
+    assert all(served)
+    want, _ = _scores(F, q, k, 8 * B * N * H)
+    for h in range(H):
+        assert_keys_close(got[0, h], want[0, h], f"{kind} h={h}")
 
 
 def test_not_finite_takes_fp64(F):
@@ -205,7 +235,7 @@ def test_prune_two_blocks_per_wave(F, d):
     _check_prune(F, "normal", q, k, rows, cols, lse, 4, (0, 5))
 
 
-@pytest.mark.parametrize("kind", ["tiny-both", "zeros", "large", "outlier", "wide"])
+@pytest.mark.parametrize("kind", ["s4", "channel", "tiny-both", "zeros", "large", "outlier", "wide"])
 def test_prune_values(F, kind):
     q, k, rows, cols, lse = _prune_state(kind, 1, 400, 2, 128, 70, 300)
     if kind == "large":
