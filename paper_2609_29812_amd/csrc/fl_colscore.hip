@@ -37,6 +37,8 @@ __device__ __forceinline__ void mfma_f64_layout(int l16, int kq, int (&row)[4], 
 // head) pairs whose values the digits do not hold, in two passes.  A wave owns 16 vectors of one side in registers
 // (lane l holds dim 4s + l / 16 of vector l % 16 for step s), the workgroup 64 of them from vector wg_first on;
 // the other side is staged 32 vectors at a time in LDS as fp64.
+// The next step's vectors are loaded into registers while a step is multiplied: 8192 x 16 heads x 128 8.88 -> 6.40 ms,
+// 32768 x 16 x 64 75.8 -> 59.4 (11.5 and 69.5 in a kernel of their own that loaded them in place).
 //   pass 1 (ROWS)  : the wave's 16 query rows against the staged K columns j <= i: per accumulator element
 //                    an online (max, sum) in fp64; the 16 partial pairs of a row are merged in column order;
 //   pass 2 (!ROWS) : the wave's 16 K columns against the staged query rows i >= j and their lse_i:
@@ -63,12 +65,12 @@ __device__ __forceinline__ void colscore_wide(const uint16_t* __restrict__ qbase
   const int v0 = wg_first + wave * 16;                  // first of the wave's own vectors
   const bool wave_ok = v0 < N;
 
-  double reg[KSTEPS];                                   // own vectors (query rows or key columns)
+  float reg[KSTEPS];                                    // own vectors (query rows or key columns), widened where used
   {
     const int v = v0 + l16;
     const uint16_t* src = (ROWS ? qbase : kbase) + (int64_t)(v < N ? v : 0) * stride + kq;
 #pragma unroll
-    for (int s = 0; s < KSTEPS; ++s) reg[s] = v < N ? (double)bf16_to_f32(src[4 * s]) : 0.0;
+    for (int s = 0; s < KSTEPS; ++s) reg[s] = v < N ? bf16_to_f32(src[4 * s]) : 0.0f;
   }
   int el_r[4], el_c[4];                   // element t: staged vector el_r (A side), own vector el_c (B side)
   mfma_f64_layout(l16, kq, el_r, el_c);
@@ -78,17 +80,31 @@ __device__ __forceinline__ void colscore_wide(const uint16_t* __restrict__ qbase
   double m[4], acc[4];
 #pragma unroll
   for (int t = 0; t < 4; ++t) { m[t] = -INFINITY; acc[t] = 0.0; }
-  __syncthreads();
-  for (int t0 = s_begin; t0 < s_end; t0 += kCsRows) {
-    for (int x = threadIdx.x; x < kCsRows * D; x += 256) {
-      const int r = x / D, dd = x % D;
-      const int v = t0 + r;
-      wide.st[r * QS + dd] = v < s_end ? (double)bf16_to_f32((ROWS ? kbase : qbase)[(int64_t)v * stride + dd]) : 0.0;
+  // the thread's elements of a step (of vectors r0, r0 + 256 / D, ..), loaded while the step before is multiplied
+  constexpr int PER = kCsRows * D / 256;
+  const int r0 = threadIdx.x / D, dd = threadIdx.x % D;
+  const rsrc_t oth = make_rsrc(ROWS ? kbase : qbase, (uint32_t)((N - 1) * stride + D) * 2u);
+  uint16_t nx[PER];
+  double nlse = 0.0;
+  auto fetch = [&](int t0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int x = 0; x < PER; ++x) {
+      const int v = t0 + r0 + x * (256 / D);            // (N H D < 2^31: 32-bit byte offsets; 0xFFFFFFFE reads zero)
+      const uint32_t off = v < s_end ? ((uint32_t)v * (uint32_t)stride + dd) * 2u : 0xFFFFFFFEu;
+      nx[x] = __builtin_amdgcn_raw_buffer_load_b16(oth, off, 0, 0);
     }
     if (!ROWS && threadIdx.x < kCsRows) {
       const int v = t0 + (int)threadIdx.x;
-      wide.lse[threadIdx.x] = v < s_end ? lse_bh[v] : 0.0;
+      nlse = v < s_end ? lse_bh[v] : 0.0;
     }
+  };
+  fetch(s_begin);
+  __syncthreads();
+  for (int t0 = s_begin; t0 < s_end; t0 += kCsRows) {
+#pragma unroll
+    for (int x = 0; x < PER; ++x) wide.st[(r0 + x * (256 / D)) * QS + dd] = (double)bf16_to_f32(nx[x]);
+    if (!ROWS && threadIdx.x < kCsRows) wide.lse[threadIdx.x] = nlse;
+    fetch(t0 + kCsRows);
     __syncthreads();
 #pragma unroll
     for (int half = 0; half < kCsRows / 16; ++half) {
@@ -99,7 +115,7 @@ __device__ __forceinline__ void colscore_wide(const uint16_t* __restrict__ qbase
         f64x4 d4 = {0.0, 0.0, 0.0, 0.0};
         const double* sa = wide.st + (16 * half + l16) * QS + kq;
 #pragma unroll
-        for (int s = 0; s < KSTEPS; ++s) d4 = __builtin_amdgcn_mfma_f64_16x16x4f64(sa[4 * s], reg[s], d4, 0, 0, 0);
+        for (int s = 0; s < KSTEPS; ++s) d4 = __builtin_amdgcn_mfma_f64_16x16x4f64(sa[4 * s], (double)reg[s], d4, 0, 0, 0);
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
           const int sv = sv0 + el_r[t];                  // staged vector
@@ -231,8 +247,9 @@ struct __attribute__((aligned(16))) CsSlot {
 // one before.  At N = 8192, 16 heads x 128: 0.73 ms a pass (11.5 -> 1.43 ms for the statistic and its lists; the fp64
 // products took 5.5 ms a pass), vector ALU 70 % and matrix cores 61 % of the busy cycles at 1.97 GHz.  Nine products
 // and a branch to four more where a digit 0 is present measured 0.95 ms: the branch ends the interleaving.
+// (three workgroups a CU also for 64-wide rows, where the fp64 products would take the registers of one of them)
 template <int D, int NB, bool ROWS>
-__global__ __launch_bounds__(256, NB == 1 ? 3 : 2) void colscore_kernel(CsArgs a, int n_wg) {
+__global__ __launch_bounds__(256, NB == 1 || (D == 64 && ROWS) ? 3 : 2) void colscore_kernel(CsArgs a, int n_wg) {
   constexpr int KS = D / 64, STG = NB == 1 ? 2 : 4;
   constexpr int BLK = 4 * KS * 64;        // 16-byte pieces of a block
   constexpr size_t kSlot = sizeof(CsSlot<D, STG>) > sizeof(CsWide<D>) ? sizeof(CsSlot<D, STG>) : sizeof(CsWide<D>);
@@ -430,13 +447,13 @@ __device__ __forceinline__ void prune_wide(const PruneArgs& a, int b, int h, int
   const int e_wave = e_first + wave * 16;                    // first entry of this wave
   const bool wave_ok = e_wave < n_ent;
   const int j_first = wave_ok ? cl[e_wave] : INT_MAX;        // entries ascend
-  double kb[KSTEPS];                       // dims 4s + kq of entry e_wave + l16 (zero past the list's end)
+  float kb[KSTEPS];                        // dims 4s + kq of entry e_wave + l16 (zero past the list's end)
   {
     const int e = e_wave + l16;
     const bool ok = e < n_ent;
     const uint16_t* src = a.k + ((int64_t)b * a.N + (ok ? cl[e] : 0)) * stride + (int64_t)h * D + kq;
 #pragma unroll
-    for (int s = 0; s < KSTEPS; ++s) kb[s] = ok ? (double)bf16_to_f32(src[4 * s]) : 0.0;
+    for (int s = 0; s < KSTEPS; ++s) kb[s] = ok ? bf16_to_f32(src[4 * s]) : 0.0f;
   }
   int el_row[4], el_ent[4];
   mfma_f64_layout(l16, kq, el_row, el_ent);
@@ -447,19 +464,37 @@ __device__ __forceinline__ void prune_wide(const PruneArgs& a, int b, int h, int
     el_j[t] = e < n_ent ? cl[e] : INT_MAX;
   }
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  __syncthreads();
-  for (int t0 = first; t0 < p_end; t0 += kPruneRows) {
-    for (int x = threadIdx.x; x < kPruneRows * D; x += 256) {
-      const int r = x / D, dd = x % D;
-      const int p = t0 + r;
-      w.qt[r * QS + dd] = p < p_end ? (double)bf16_to_f32(a.q[((int64_t)b * a.N + s_rows[p - p0]) * stride + (int64_t)h * D + dd]) : 0.0;
+  // the thread's elements of a step (of rows r0, r0 + 256 / D, ..), loaded while the step before is multiplied
+  constexpr int PER = kPruneRows * D / 256;
+  const int r0 = threadIdx.x / D, dd = threadIdx.x % D;
+  const rsrc_t qb = make_rsrc(a.q + (int64_t)b * a.N * stride + (int64_t)h * D, (uint32_t)((a.N - 1) * stride + D) * 2u);
+  uint16_t nx[PER];
+  int nrow = -1;
+  float nlse = 0.0f;
+  auto fetch = [&](int t0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int x = 0; x < PER; ++x) {
+      const int p = t0 + r0 + x * (256 / D);
+      // (N H D < 2^31: 32-bit byte offsets; 0xFFFFFFFE reads zero)
+      const uint32_t off = p < p_end ? ((uint32_t)s_rows[p - p0] * (uint32_t)stride + dd) * 2u : 0xFFFFFFFEu;
+      nx[x] = __builtin_amdgcn_raw_buffer_load_b16(qb, off, 0, 0);
     }
     if (threadIdx.x < kPruneRows) {
       const int p = t0 + (int)threadIdx.x;
-      const int i = p < p_end ? s_rows[p - p0] : -1;
-      w.row[threadIdx.x] = i;
-      w.lse[threadIdx.x] = p < p_end ? (double)a.lse_ref[((int64_t)b * a.N + i) * a.H + h] : 0.0;
+      nrow = p < p_end ? s_rows[p - p0] : -1;
+      nlse = p < p_end ? a.lse_ref[((int64_t)b * a.N + nrow) * a.H + h] : 0.0f;
     }
+  };
+  fetch(first);
+  __syncthreads();
+  for (int t0 = first; t0 < p_end; t0 += kPruneRows) {
+#pragma unroll
+    for (int x = 0; x < PER; ++x) w.qt[(r0 + x * (256 / D)) * QS + dd] = (double)bf16_to_f32(nx[x]);
+    if (threadIdx.x < kPruneRows) {
+      w.row[threadIdx.x] = nrow;
+      w.lse[threadIdx.x] = (double)nlse;
+    }
+    fetch(t0 + kPruneRows);
     __syncthreads();
 #pragma unroll
     for (int half = 0; half < kPruneRows / 16; ++half) {
@@ -469,7 +504,7 @@ __device__ __forceinline__ void prune_wide(const PruneArgs& a, int b, int h, int
         f64x4 d4 = {0.0, 0.0, 0.0, 0.0};
         const double* qa = w.qt + (16 * half + l16) * QS + kq;
 #pragma unroll
-        for (int s = 0; s < KSTEPS; ++s) d4 = __builtin_amdgcn_mfma_f64_16x16x4f64(qa[4 * s], kb[s], d4, 0, 0, 0);
+        for (int s = 0; s < KSTEPS; ++s) d4 = __builtin_amdgcn_mfma_f64_16x16x4f64(qa[4 * s], (double)kb[s], d4, 0, 0, 0);
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
           const int r = 16 * half + el_row[t];
@@ -496,8 +531,8 @@ __device__ __forceinline__ void prune_wide(const PruneArgs& a, int b, int h, int
 // A wave owns NB blocks of 16 entries as digits in registers, a workgroup 64 NB entries; the chunk's rows are turned
 // into digits 64 at a time (16 per wave) into LDS, the rows of the next 64 on their way while these are multiplied.
 // Where the digits do not serve the rows and entries of the workgroup, or a log-normaliser is out of their range, the
-// workgroup takes fp64 products.  At 1638 rows and 1532 entries of 16 heads x 128: 366 us in fp64 products (their matrix
-// rate), 105 us so.
+// workgroup takes fp64 products.  At 1638 rows and 1532 entries of 16 heads x 128: 103 us by digits; by fp64 products
+// after them 256 us (358 where a step's rows were loaded in place; 308 in a kernel of their own that did the same).
 template <int D, int NB>
 __global__ __launch_bounds__(256, 2) void prune_mass_kernel(PruneArgs a) {
   constexpr int KS = D / 64;

@@ -75,7 +75,7 @@ def _scores(F, q, k, ws_bytes=None):
     assert rc == 0
     pairs = B * H
     first, stride = (pairs - 1) // n * n, -(-N // 16) * 16
-    if size < need:
+    if size < need or (q.data_ptr() | k.data_ptr()) % 16:
         first, stride = 0, N
     lse = ws[:(pairs - first) * stride * 8].view(torch.float64).view(-1, stride)[:, :N]
     rows = torch.linspace(0, N - 1, min(N, 9), device="cuda").round().long()
@@ -202,6 +202,32 @@ def test_small_workspace(F):
     for b in range(2):
         for h in range(3):
             assert_keys_close(got[b, h], want[b, h], f"b={b} h={h}")
+
+
+def _misaligned(x):
+    """The same tensor one element (2 bytes) past a 16-byte boundary."""
+    y = torch.empty(x.numel() + 8, dtype=x.dtype, device="cuda")[1:1 + x.numel()].view(x.shape)
+    assert y.data_ptr() % 16 == 2
+    return y.copy_(x)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_misaligned(F, d):
+    """Queries or keys off the 16-byte boundary take the fp64 products, in both statistics."""
+    q, k, rows, cols, lse = _prune_state("normal", 2, 333, 3, d, 70, 290)
+    q, k = up_bf16(q), up_bf16(k)
+    rows, cols, lse = (torch.from_numpy(x).cuda() for x in (rows, cols, lse))
+    want, served = _scores(F, q, k)
+    list_want = down(F.prune_columns(q, k, rows, cols, lse, 4, 5)[1])
+    assert all(served)
+    for mq, mk in ((_misaligned(q), k), (q, _misaligned(k))):
+        got, served = _scores(F, mq, mk, F.load().fl_column_scores_ws(2, 333, 3))
+        assert not any(served)
+        list_got = down(F.prune_columns(mq, mk, rows, cols, lse, 4, 5)[1])
+        for b in range(2):
+            for h in range(3):
+                assert_keys_close(got[b, h], want[b, h], f"b={b} h={h}")
+                assert_keys_close(list_got[b, h], list_want[b, h], f"list b={b} h={h}")
 
 
 # ---- the list statistic -----------------------------------------------------------------------------------
