@@ -9,8 +9,8 @@
 namespace fl {
 
 constexpr int kBN = 32;            // columns per tile
-// cache policy of tile loads that few workgroups share (the band): non-temporal (the "nt" bit, 2 on gfx950); measured a
-// few percent faster than the default policy on the 32K workload
+// cache policy of the tile loads of fl_attn.hip's kernels: non-temporal (the "nt" bit, 2 on gfx950); measured a few
+// percent faster there than the default policy on the 32K workload (the segment kernels take the default one)
 constexpr int kDmaPolicy = 2;
 
 typedef __amdgpu_buffer_rsrc_t rsrc_t;

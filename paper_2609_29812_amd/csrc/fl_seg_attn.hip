@@ -38,7 +38,6 @@
 #include "fl_attn_util.h"
 
 #include <algorithm>
-#include <type_traits>
 
 namespace fl {
 
@@ -244,14 +243,13 @@ __device__ __forceinline__ void seg_body(const SegArgs& a) {
     lcol[t] = inst * CPI + lane / CH;
     lsw[t] = (uint32_t)((lane % CH) ^ swz32_f<D>(lcol[t])) * 16 + head_off;
   }
-  struct Offs { uint32_t o[NIK]; bool list; };
+  struct Offs { uint32_t o[NIK]; };
   // (the descriptor of position u is passed in: the step reads the next DMA tile's a step ahead)
   auto tile_offs_d = [&](int u, int2 dsc) __attribute__((always_inline)) {
     Offs r;
     const bool have = u < n_tiles;
     const int dx = __builtin_amdgcn_readfirstlane(dsc.x), dy = __builtin_amdgcn_readfirstlane(dsc.y);
     const bool in_list = dx >= 0;
-    r.list = in_list;                     // uniform
     const int f = dx & 0x7FFFFFFF;
     const int hi = (have & !((dy >> 21) & 1)) ? (dy >> 16) & 31 : -1;   // tile columns c <= hi exist
     const int fl = (in_list & (hi >= 0)) ? f : 0;
@@ -266,23 +264,19 @@ __device__ __forceinline__ void seg_body(const SegArgs& a) {
   auto tile_offs = [&](int u) __attribute__((always_inline)) {
     return tile_offs_d(u, tdesc[u < n_tiles ? u : 0]);
   };
-  // List tiles with the default cache policy, as every segment of the head reads them; band tiles, which one or two
-  // segments read, non-temporal.  Against non-temporal loads of both: 16K batch-4 loop 2 (3277 rows, 1024 columns)
-  // subtract pass 150 -> 145 us, add pass 201 -> 193; the 32K layer 521 -> 513 us.
-  auto issue_as = [&](Slot<D>& sl, const Offs& of, auto policy) __attribute__((always_inline)) {
+  // All tiles with the default cache policy: every segment of the head reads the list tiles.  Subtract / add pass against
+  // non-temporal loads: 16K batch 4 (one team, 3277 rows, 1024 columns) 105 / 151 us against 117 / 158; two teams: 32K
+  // (1638 rows, 1536 columns, window 512) 77.9 / 84.4 against 80.6 / 87.1, 8K (550 rows, 1024 columns) 19.7 / 26.5
+  // against 19.8 / 26.3, 4K (410 rows, 448 columns, window 64) 23.9 / 31.0 against 23.6 / 30.5.  List tiles one way and
+  // band tiles the other, by a branch a step: 80.3 / 86.4, 20.3 / 27.1 and 24.6 / 31.6.
+  auto issue = [&](Slot<D>& sl, const Offs& of) __attribute__((always_inline)) {
 #pragma unroll
     for (int t = 0; t < NI; ++t) {
       const int inst = w4 * NIK + (t % NIK);
       const uint32_t off = of.o[t % NIK];
-      if (t < NIK)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(kcR, FL_LDS(sl.k + tofs + inst * 512), 16, off, 0, 0, policy.value);
-      else
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(vcR, FL_LDS(sl.v + tofs + inst * 512), 16, off, 0, 0, policy.value);
+      if (t < NIK) __builtin_amdgcn_raw_ptr_buffer_load_lds(kcR, FL_LDS(sl.k + tofs + inst * 512), 16, off, 0, 0, 0);
+      else __builtin_amdgcn_raw_ptr_buffer_load_lds(vcR, FL_LDS(sl.v + tofs + inst * 512), 16, off, 0, 0, 0);
     }
-  };
-  auto issue = [&](Slot<D>& sl, const Offs& of) __attribute__((always_inline)) {
-    if (TEAMS == 1 || of.list) issue_as(sl, of, std::integral_constant<int, 0>{});
-    else issue_as(sl, of, std::integral_constant<int, kDmaPolicy>{});
   };
 
   // LDS read offsets (elements).  K (A operand of S^T = K Q^T): row r32, data chunk 2 ks + hw.  V
