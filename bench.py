@@ -36,7 +36,8 @@ if ROOT not in sys.path:
 METRIC = "updated-token attn rows/s per layer-loop + achieved HBM GB/s & MFMA % at 32K"
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E
 MFMA_BF16_TFLOPS = 2500.0      # dense bf16/fp16 MFMA
-FP64_VECTOR_TFLOPS = 78.6      # fp64 vector FMA (the pruning statistic)
+MFMA_I8_TOPS = 5000.0          # dense i8 MFMA (the pruning statistic)
+DIGIT_PRODUCTS = 13            # i8 products per 64-bit dot product (csrc/fl_digits.h)
 PROFILE_DIR = os.path.join(ROOT, "profiles")
 
 
@@ -790,12 +791,12 @@ def decode_bench(w, gs, fl, torch):
             "dense_loop_us": round(us_dense, 2), "sparse_loop_us": round(us_sparse, 2),
             "dense_alg_MB": round(nb_dense / 1e6, 2), "sparse_alg_MB": round(nb_sparse / 1e6, 2),
             "dense_GBps": round(nb_dense / us_dense / 1e3, 1), "sparse_GBps": round(nb_sparse / us_sparse / 1e3, 1),
-            "timing": f"HIP events, mean of {reps} calls (two launches each, nothing allocated)"}
+            "timing": f"HIP events, mean of {reps} calls (two or three launches each, nothing allocated)"}
 
 
 def prune_work(rows, cols, n_sink, H, d):
     """Algorithmic work of one fl_prune_columns call: bytes = the list entries' K rows, the updated rows'
-    queries and lse_ref, the keys written, the lists read and written; fp64 flops = 2 d per (updated row i,
+    queries and lse_ref, the keys written, the lists read and written; flops = 2 d per (updated row i,
     list entry j >= sinks) pair with i >= j (one dot product each; the exponentials are not counted)."""
     B, k = rows.shape
     c_list = cols.shape[2]
@@ -827,13 +828,14 @@ def prune_bench(w, gs, q_last, fl, torch):
     us = e0.elapsed_time(e1) / reps * 1e3
     B, N, H, d = gs.k_hat.shape
     nb, nf = prune_work(gs.cand.cpu().numpy(), gs.cols.cpu().numpy(), w.n_sink, H, d)
-    achieved = nf / (us * 1e-6) / 1e12
-    log(f"[bench] prune: {us:.1f} us, {achieved:.2f} fp64 TFLOP/s")
+    achieved = DIGIT_PRODUCTS * nf / (us * 1e-6) / 1e12
+    log(f"[bench] prune: {us:.1f} us, {achieved:.0f} i8 TOP/s ({achieved / DIGIT_PRODUCTS:.1f} TFLOP/s of dot products)")
     return {"workload": f"{w.name} list {gs.cols.shape[2]} -> {min(w.n_sink, gs.cols.shape[2]) + t_next} entries "
                         f"over {gs.cand.shape[1]} updated rows", "us": round(us, 2),
-            "bound": "alu", "achieved": round(achieved, 2), "peak": FP64_VECTOR_TFLOPS, "unit": "TFLOP/s (fp64)",
-            "frac": round(achieved / FP64_VECTOR_TFLOPS, 4), "alg_MB": round(nb / 1e6, 2),
-            "alg_GF": round(nf / 1e9, 3), "timing": f"HIP events, mean of {reps} calls (two launches each)"}
+            "bound": "mfma", "achieved": round(achieved, 2), "peak": MFMA_I8_TOPS,
+            "unit": f"TOP/s (i8, {DIGIT_PRODUCTS} products per 64-bit dot product)",
+            "frac": round(achieved / MFMA_I8_TOPS, 4), "alg_MB": round(nb / 1e6, 2),
+            "alg_GF": round(nf / 1e9, 3), "timing": f"HIP events, mean of {reps} calls (three launches each)"}
 
 
 def tail_bench(w, gs, k_last, fl, torch, tail=64):

@@ -46,7 +46,7 @@ def check(idx, cols, slot, N, H, d, w, B, reuse, current):
 
 
 def test_prune_work_counts_match_brute_force():
-    """fl_prune_columns: one d-long fp64 dot product per (updated row i, non-sink entry j) with i >= j."""
+    """fl_prune_columns: one d-long dot product per (updated row i, non-sink entry j) with i >= j."""
     rng = np.random.default_rng(1)
     B, N, H, d, ns = 2, 400, 3, 64, 4
     rows = np.stack([np.sort(rng.choice(N, 50, replace=False)) for _ in range(B)]).astype(np.int32)
