@@ -121,8 +121,13 @@ def _p(t):
     return None if t is None else t.data_ptr()
 
 
-def _stream():
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+# (the C call is private to torch; without it the public form)
+if hasattr(torch._C, "_cuda_getCurrentRawStream") and hasattr(torch._C, "_cuda_getDevice"):
+    def _stream():
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+else:
+    def _stream():
+        return torch.cuda.current_stream().cuda_stream
 
 
 def _dev(t, dtype, name, shape=None):

@@ -54,3 +54,9 @@ def test_graph_replay_matches_eager_steps(F, name, over):
         scratch = torch.empty(1 << 20, device="cuda").normal_()
         float(scratch.sum())
     say(f"  {step + 1} replays bit-identical to the eager steps")
+
+
+def test_calls_take_the_current_stream(F):
+    for s in (torch.cuda.current_stream(), torch.cuda.Stream()):
+        with torch.cuda.stream(s):
+            assert F._stream() == torch.cuda.current_stream().cuda_stream == s.cuda_stream
