@@ -3,16 +3,16 @@
 // All kernels stream rows with 16-byte loads: one thread owns 8 consecutive channels of a row, so codes
 // of those channels form one 2/4/8-byte word (LSB-first packing) and metadata loads are 2 or 16 bytes.
 //   quant_token   (keys, per-channel groups of G packed rows): a 256-thread workgroup owns one group of
-//                 rows x 256 channels; 8 row slices reduce min/max through LDS, then the same threads
-//                 encode their rows from registers (no second pass over HBM).
-//   quant_channel (values, per-token groups of G channels): the G/8 threads of a group reduce min/max
-//                 with lane shuffles.
+//                 rows x 64 channels (256 at G = 8, 128 at G = 16); its row slices (G of them, at most 32)
+//                 reduce min/max in registers and LDS, then the same threads encode their rows from registers
+//                 (no second pass over HBM).
+//   quant_channel (values, per-token groups of G channels): the G/8 lanes of a group reduce min/max by DPP.
 //   dequant       rebuilds bf16(x_hat + z + q*s) rows, compact or in place.
 // Both quantizers optionally write the reconstructed rows (fusing the compact dequantization).
 //
 // The quantizers are bound by vector instructions as much as by HBM (a 32K base of 16 heads x 128 in 4 bits moves
-// 620 MB, 118 us at the rate of a large copy): per value about 50 instructions, of which a third for the group's
-// metadata in fp64 and a 64-bit division for the row, took 158 us; 31 a value, the count now, take 130 us.
+// 620 MB, 118 us at the rate of a large copy): 42 vector instructions a value, a third of them
+// for the group's metadata in fp64 and a 64-bit division for the row, took 150 us; 31 a value, the count now, take 132.
 #include "fl_attn_util.h"
 
 namespace fl {
