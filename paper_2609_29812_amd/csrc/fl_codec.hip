@@ -133,7 +133,7 @@ __device__ __forceinline__ GroupMeta group_meta(float mn, float mx) {
   const float bb = d - mx;                                 // TwoSum: the rounding error of d
   const float err = (mx - (d - bb)) + (-m.z - bb);
   constexpr float q = (float)QMAX, rq = 1.0f / q;
-  m.sb = f16_towards_zero(fminf(d * rq, 65504.0f));
+  m.sb = f16_towards_zero(fminf(d * rq, 65504.0f)) & 0x7FFFu;   // (a group of -0 has d = -0)
   m.sb += f16_bits_to_f32(m.sb) * q < d ? 1u : 0u;
   m.sb += f16_bits_to_f32(m.sb) * q < d ? 1u : 0u;
   m.sb = min(m.sb, 0x7BFFu);

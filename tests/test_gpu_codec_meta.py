@@ -60,3 +60,22 @@ def test_metadata(F, bits, axis, group):
         assert np.array_equal(down(scale).view(np.uint16), f16_bits(enc["scale"]))
         assert np.array_equal(down(codes), enc["codes"])
         assert np.array_equal(down_bits16(out), new)
+
+
+@pytest.mark.parametrize("axis", [codec.AXIS_TOKEN, codec.AXIS_CHANNEL])
+@pytest.mark.parametrize("kind", ["-0", "-0 and 0", "-0 - 0"])
+def test_negative_zeros(F, axis, kind):
+    """Groups of zeros of either sign, whose range may be -0: zero and scale are +0."""
+    B, N, H, d, bits, group = 1, 72, 2, 64, 4, 8
+    cur = np.full((B, N, H, d), 0x8000, np.uint16)
+    if kind == "-0 and 0":
+        cur[:, ::3, :, 5::7] = 0
+    ref = np.zeros_like(cur) if kind == "-0 - 0" else None
+    enc = codec.quantize(cur, ref, None, bits, group, axis)
+    _, new = codec.reconstruct(ref, cur, None, enc, bits, group, axis)
+    codes, scale, zero, out = F.kv_residual_quant(up_bf16(cur), None if ref is None else up_bf16(ref), None, bits, group, axis)
+    torch.cuda.synchronize()
+    assert np.array_equal(down(zero).view(np.uint16), f16_bits(enc["zero"]))
+    assert np.array_equal(down(scale).view(np.uint16), f16_bits(enc["scale"]))
+    assert np.array_equal(down(codes), enc["codes"])
+    assert np.array_equal(down_bits16(out), new)
