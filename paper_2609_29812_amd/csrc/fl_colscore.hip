@@ -245,8 +245,8 @@ struct __attribute__((aligned(16))) CsSlot {
 // Bound by issue on both pipes: per 16 x 16 block and wave, 26 i8 products (416 matrix cycles) and about 95 vector
 // instructions (380 cycles) at d = 128, so the products of one block are issued between the exponentials of the
 // one before.  At N = 8192, 16 heads x 128: 11.5 -> 1.43 ms for the statistic and its lists (a pass took 5.5 ms in fp64
-// products, 0.7 now; 0.76 at least and 0.81 in the median under the profiler), vector ALU 65 % and matrix cores 56 % of
-// the busy cycles at 1.88 GHz.  Nine products and a branch to four more where a digit 0 is present measured 0.95 ms:
+// products, 0.7 now; 0.75 at least and 0.80 in the median under the profiler), vector ALU 65 % and matrix cores 56 % of
+// the busy cycles at 1.9 GHz.  Nine products and a branch to four more where a digit 0 is present measured 0.95 ms:
 // the branch ends the interleaving.
 // (three workgroups a CU also for 64-wide rows, where the fp64 products would take the registers of one of them)
 template <int D, int NB, bool ROWS>

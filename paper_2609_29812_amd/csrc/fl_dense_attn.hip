@@ -10,8 +10,8 @@
 //
 // Bound by the vector ALU beside the matrix cores: per 32 rows x 64 columns at d = 128, 32 products (1024 matrix cycles)
 // against about 170 vector instructions and 32 exponentials (1200 cycles), overlapped by two waves per SIMD of
-// independent workgroups; at N = 16384, 16 heads the clock falls to 1.6 GHz, the matrix cores are busy 51 % of its cycles.
-// 16 heads x 128: N = 16384 1.41 -> 1.16 ms (945 TFLOP/s), N = 4096 158 -> 103 us; 3 x 1009 rows of 8 heads x 64
+// independent workgroups; at N = 16384, 16 heads the clock falls to 1.6 GHz, the matrix cores are busy 50 % of its cycles.
+// 16 heads x 128: N = 16384 1.41 -> 1.15 ms (955 TFLOP/s), N = 4096 158 -> 103 us; 3 x 1009 rows of 8 heads x 64
 // 25 -> 14 us, against 32-column stages of a four-slot ring with tables and an LDS conversion of V each step.
 #include "fl_attn_util.h"
 

@@ -6,9 +6,9 @@
 // selected positions are bits of one word and one block scan gives their places in the output.  The k-th largest key is
 // found by an LDS histogram over the keys' range, whose bin is compacted into LDS and resolved by digit histograms.
 //
-// Bound by latency: one workgroup, a chain of barriers.  32K keys (k = 1638, with the slot map): 23 us with keys
-// held in stripes, whose output order took ballot bitmaps through LDS, and LDS-permute scans; 18.7 us so (8K keys 15.7 against 10.2, 256 keys
-// 7.9 against 4.5).
+// Bound by latency: one workgroup, a chain of barriers.  32K keys (k = 1638, with the slot map): 18.7 us, 23 with keys
+// held in stripes, whose output order took ballot bitmaps through LDS, and LDS-permute scans (8K keys 10.2 against 15.7,
+// 256 keys 4.5 against 7.9).
 #pragma once
 #include "fl_common.h"
 
