@@ -448,7 +448,7 @@ def dense_attn(q, k_cache, v_cache, o=None, lse=None, sm_scale=None):
 
 
 def column_scores(q, k_cache):
-    """fp32 column keys [B, H, N] of a dense source loop (fp64 inside)."""
+    """fp32 column keys [B, H, N] of a dense source loop (64-bit sums inside)."""
     B, N, H, d = q.shape
     _dev(q, torch.bfloat16, "q")
     _dev(k_cache, torch.bfloat16, "k_cache", q.shape)
